@@ -8,8 +8,15 @@
 // into LDS differs.  A workgroup owns a BM x BN output tile and walks the contraction in steps of 64.  Its eight
 // waves are specialised: four staging waves move packed words global -> registers -> (unpack, s*(q-z), round to
 // 16 bit) -> LDS (two stages); four MFMA waves pull the activation tile global -> LDS directly (three stages, no
-// registers) and read 16-byte fragments of both operands into v_mfma_f32_32x32x16.  One barrier per stage.
+// registers) and read 16-byte fragments of both operands into v_mfma_f32_16x16x32.  One barrier per stage.
 // The dequantised weight never reaches HBM.  The rank-r LoRA term is folded in as extra contraction steps.
+//
+// What bounds the large launches is power: the matrix pipe's clock falls with the operand bits that change.  A
+// register-resident loop on random fp16 operands sustains 1590 TFLOP/s with 32x32x16 MFMAs and 1870 with 16x16x32 (half
+// the accumulator traffic per flop; bf16 1770 and 2015).  The 16x16x32 form, weights as the first operand and the MFMAs
+// of a step in serpentine order take the fp16 step at 2048 x 4096 x 4096, INT4, from 153 to 144 us, 4096 x 11008 -> 4096,
+// INT3, from 725 to 679 us and the bf16 forward pass at 8192 x 4096 -> 11008 from 725 to 693 us; launches of 128-row
+// tiles, which are too short to be held back by power, take the same time as before.
 // Launches that give every compute unit at least one 256 x 256 tile use a second arrangement of the same parts
 // (SYM below): eight waves that each stage, load and multiply an eighth.
 #include "common.hpp"
@@ -44,13 +51,13 @@ struct GemmArgs {
 };
 
 template <bool BF16>
-__device__ __forceinline__ float16_t mfma32(u16x8_t a, u16x8_t b, float16_t c)
+__device__ __forceinline__ float4_t mfma16(u16x8_t a, u16x8_t b, float4_t c)
 {
     if constexpr (BF16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                        c, 0, 0, 0);
     else
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c,
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c,
                                                       0, 0, 0);
 }
 
@@ -86,7 +93,6 @@ struct StageRegs {
     uint32_t w[WU][BITS];
     uint16_t s[WU];     // raw fp16 bits: nothing may touch loaded values before they are staged, or the
     uint8_t z[WU];      // in-order memory counter would make that instruction wait for every load issued so far
-    bool ok[WU];        // false: the unit lies outside the weight, stage zeros
 };
 
 // wait until at most N vector-memory operations of this wave are outstanding, then meet the workgroup
@@ -100,7 +106,7 @@ __device__ __forceinline__ void wait_vm_and_barrier()
 // rows starting at a multiple of 4 (the transposing reads), its lower three bits through 0..7 over any 8 consecutive
 // rows starting at a multiple of 8 (the 16-byte writes, one row per lane: eight lanes per clock into a bank space of
 // 128 bytes.  Counters: with a key whose lower three bits took four values, a write took 16 LDS cycles instead of 8).
-__device__ __forceinline__ constexpr int wswz(int row) { return ((row & 3) << 2) | (row & 2) | ((row >> 2) & 1); }
+__device__ __forceinline__ constexpr int wswz(int row) { return ((row & 3) << 2) | ((row & 2) ^ ((row >> 2) & 2)) | ((row >> 2) & 1); }
 // Slot key of a row of the forward weight stage of the symmetric arrangement (128-byte rows): eight different values
 // over the even and over the odd rows of any 16 consecutive rows (16-byte reads: sixteen lanes per clock, two rows
 // fill the 256-byte bank space), four different values mod 4 over any 4 consecutive rows (16-byte writes: two
@@ -112,10 +118,11 @@ __device__ __forceinline__ constexpr int fswz(int row) { return ((row & 3) ^ ((r
 // staging waves lay the tile's rows of u and columns of A (both fetched at kernel start) beside the epilogue area, and
 // the copy-out adds the masked product to every 8-element piece before it is stored.
 //
-// SYM (256 x 256 tiles, for launches of at least one such tile per compute unit): four waves, one per SIMD, each with
-// a 128 x 128 block of accumulators (256 registers, which leaves no room for a second wave on the SIMD) and each
-// doing a quarter of everything: activation loads, weight staging and the MFMAs.  Twice the flops per byte moved
-// through LDS and through the direct-to-LDS path of the 256 x 128 tile.
+// SYM (256 x 256 tiles, for launches of at least one such tile per compute unit): eight waves, two per SIMD, each with
+// a 128 x 64 block of accumulators and each doing an eighth of everything: activation loads, weight staging and the
+// MFMAs.  The accumulators are half of a wave's 256 registers; a spilled register would be reloaded through the
+// vector-memory counter that the stages wait on (a build with a dozen spills took 1.4 times as long), so addresses are
+// formed when they are needed, two sets of packed words are in flight and two block rows of fragments are held.
 template <int BITS, bool BF16, bool TRANS, int BM, int BN, int WM, int WN, bool MASKED = false, bool SYM = false>
 __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kernel(const GemmArgs a)
 {
@@ -127,7 +134,11 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     constexpr int NSTG = SYM ? MW * 64 : STAGERS;   // staging threads: all of them, or the four staging waves
     static_assert(BN % 128 == 0 && BM % 128 == 0, "tile shape");
     constexpr int TM = BM / WM, TN = BN / WN;       // per-wave output tile
-    constexpr int MI = TM / 32, NI = TN / 32;       // 32x32 MFMA blocks per wave
+    constexpr int MI = TM / 16, NI = TN / 16;       // 16x16 MFMA blocks per wave
+    // block rows multiplied from one set of fragments (SYM: the staging registers leave room for two), sets per k-step
+    constexpr int MH = SYM ? 2 : 4, AH = MI / MH;
+    static_assert(MI % MH == 0, "a stage is made of whole steps of MH x NI MFMAs");
+    constexpr int STEPS = AH * BK / 32;             // such steps per stage
     constexpr int XDMA = BM / 8 / MW;               // direct-to-LDS loads per MFMA wave per stage (8 rows each)
     static_assert(XDMA >= 4 && XDMA % 4 == 0, "loads are spread over the four k-steps");
     constexpr int WU = 2 * BN / NSTG;               // 32-code weight units per staging thread per stage
@@ -190,127 +201,171 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     }
     const int row0 = pm * BM, col0 = pn * BN;
 
-    float16_t acc[MI][NI];
+    float4_t acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < NI; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     // Activation tile in LDS: row r is 128 bytes = eight 16-byte slots; slot s holds the row's chunk
     // s ^ ((r >> 1) & 7).  A 16-byte LDS read serves 16 lanes per clock out of a 256-byte-wide bank space, i.e. two
     // rows; with this key the 16 consecutive rows read by 16 lanes fall into 16 different slots of that space.
     // A direct-to-LDS load lays the 64 lanes' 16 bytes down contiguously (8 rows), so the swizzle is applied by
     // choosing which global chunk each lane fetches.
-    struct Frags {
-        u16x8_t a[MI], b[NI];
+    // A step multiplies MH block rows of the activation tile with all NI block columns of the weight tile over 32
+    // contraction elements; a k-step of 32 is AH steps that share the weight fragments.
+    struct AFrags {
+        u16x8_t a[MH];
     };
-    const int fr = lane & 31, fh = lane >> 5;
-    int aoff[BK / 16];                              // per k-step: this lane's offset into an activation stage
+    struct BFrags {
+        u16x8_t b[NI];
+    };
+    const int fr = lane & 15, fq = lane >> 4;
+    int aoff[BK / 32];                              // per k-step: this lane's offset into an activation stage
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) aoff[ks] = (wm * TM + fr) * BK + ((2 * ks + fh) ^ ((fr >> 1) & 7)) * 8;
-    // and into a weight stage (a k-step adds 16 contraction elements).  Transposing read: in every block of 16
+    for (int ks = 0; ks < BK / 32; ++ks) aoff[ks] = (wm * TM + fr) * BK + ((4 * ks + fq) ^ ((fr >> 1) & 7)) * 8;
+    // and into a weight stage (a k-step adds 32 contraction elements).  Transposing read: in every block of 16
     // lanes, lane 4e+g supplies the address of four consecutive 16-bit columns of one row, and lane i receives, as
     // element e, column i%4 of the row supplied by lane 4e + i/4.  Lane (e, g) of block b therefore points at row
-    // 8 (b/2) + e, columns 16 (b%2) + 4g .. +4 of the 16 x 32 k-step slab, and lane l ends up with contraction
-    // elements 8 (l/32) .. +4 of column l % 32: half an MFMA operand; the second read starts four rows further down.
-    // The row's swizzle key is 4 e + 2 (l/32) + (second read), so each of the 2 NI reads has its own offset.
-    const int boff = TRANS ? 0 : (wn * TN + fr) * WPITCH + (SYM ? 0 : fh * 8);
-    int toff[TRANS ? NI : 1][2];
+    // 8 b + e, columns 4g .. +4 of the 32 x 16 slab of a block column, and lane l ends up with contraction elements
+    // 8 (l/16) .. +4 of column l % 16: half an MFMA operand; the second read starts four rows further down.
+    // The row's swizzle key differs between the two reads, so each of the 2 NI reads has its own offset.
+    const int boff = TRANS ? 0 : (wn * TN + fr) * WPITCH + (SYM ? 0 : fq * 8);
+    uint32_t toff[2] = {0, 0};                      // byte offsets for block column 0; block column j: ^ 32 j
     if constexpr (TRANS) {
-        const int e = (lane & 15) >> 2, row = 8 * (lane >> 5) + e;
-        const int piece = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);     // 16-byte piece within the 64-byte run
+        const int row = 8 * (lane >> 4) + ((lane & 15) >> 2);
+        const int piece = (lane & 3) >> 1;                               // 16-byte piece within the 32-byte run
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi)
-                toff[j][hi] = (row + 4 * hi) * WPITCH
-                            + (((wn * TN / 8 + 4 * j + piece) ^ wswz(row + 4 * hi)) * 8) + 4 * (lane & 1);
+        for (int hi = 0; hi < 2; ++hi)
+            toff[hi] = (uint32_t)((row + 4 * hi) * WPITCH * 2 + ((wn * TN / 8 + piece) ^ wswz(row + 4 * hi)) * 16 + 8 * (lane & 1));
+        static_assert(!TRANS || TN == 64, "the pieces of a wave's block columns differ in slot bits 1 and 2 only");
     }
-    auto load_frags = [&](int xstage, int wstage, int ks, Frags &f) {
-        const uint16_t *As = xs + xstage * XS + aoff[ks];
+    auto load_a = [&](int xstage, int ks, int half, AFrags &f) {
+        const uint16_t *As = xs + xstage * XS + aoff[ks] + half * MH * 16 * BK;
 #pragma unroll
-        for (int i = 0; i < MI; ++i) f.a[i] = *(const u16x8_t *)(As + i * 32 * BK);
+        for (int i = 0; i < MH; ++i) f.a[i] = *(const u16x8_t *)(As + i * 16 * BK);
+    };
+    auto load_b = [&](int wstage, int ks, BFrags &f) {
         if constexpr (TRANS) {
-            const uint16_t *Bs = wsm + wstage * WS + ks * 16 * WPITCH;   // 16 rows further: same swizzle keys
+            const uint8_t *Bs = (const uint8_t *)(wsm + wstage * WS + ks * 32 * WPITCH);   // 32 rows further: same swizzle keys
+            uint32_t t0 = toff[0], t1 = toff[1];
+            if constexpr (SYM) asm("" : "+v"(t0), "+v"(t1));            // formed when needed: registers are short
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 typedef short s16x4_t __attribute__((ext_vector_type(4)));
                 typedef __attribute__((address_space(3))) s16x4_t *lds4_t;
-                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(Bs + toff[j][0]));
-                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(Bs + toff[j][1]));
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(Bs + (t0 ^ (32u * j))));
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(Bs + (t1 ^ (32u * j))));
                 f.b[j] = u16x8_t{(uint16_t)lo[0], (uint16_t)lo[1], (uint16_t)lo[2], (uint16_t)lo[3],
                                  (uint16_t)hi[0], (uint16_t)hi[1], (uint16_t)hi[2], (uint16_t)hi[3]};
             }
         } else {
-            // (SYM: the slot key depends on the row's lower four bits: the same 32 rows further down)
-            const uint16_t *Bs = wsm + wstage * WS + boff + (SYM ? ((2 * ks + fh) ^ fswz(fr)) * 8 : ks * 16);
+            // (SYM: the slot key depends on the row's lower four bits: the same 16 rows further down)
+            const uint16_t *Bs = wsm + wstage * WS + boff + (SYM ? ((4 * ks + fq) ^ fswz(fr)) * 8 : ks * 32);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) f.b[j] = *(const u16x8_t *)(Bs + j * 32 * WPITCH);
+            for (int j = 0; j < NI; ++j) f.b[j] = *(const u16x8_t *)(Bs + j * 16 * WPITCH);
         }
     };
-    auto mfma_frags = [&](const Frags &f) {
+    // The weight is the MFMA's first operand: a lane then holds four neighbouring output columns of one token row.  The
+    // order of a step's MFMAs is a serpentine, so that each shares one operand with the one before: what the matrix
+    // pipe draws, and with it the clock, follows how many operand bits change (register-resident loop on random fp16
+    // operands: 1835 TFLOP/s in plain order, 1934 as a serpentine).
+    auto mfma_step = [&](int half, const AFrags &fa, const BFrags &fb) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MH; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j) acc[i][j] = mfma32<BF16>(f.a[i], f.b[j], acc[i][j]);
+            for (int jj = 0; jj < NI; ++jj) {
+                const int j = (i & 1) ? NI - 1 - jj : jj;
+                acc[half * MH + i][j] = mfma16<BF16>(fb.b[j], fa.a[i], acc[half * MH + i][j]);
+            }
+    };
+    // a step's MFMAs with the LDS reads of later steps slotted between them, one behind each MFMA
+    auto spread = [&](int reads) {
+#pragma unroll
+        for (int i = 0; i < MH * NI; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        // one MFMA
+            if (i < reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);         // one LDS read
+        }
+    };
+    constexpr int A_READS = MH, B_READS = TRANS ? 2 * NI : NI;
+    AFrags fa[2];
+    BFrags fb[2];
+    // The steps of one stage.  `work(s)` runs before step s's MFMAs are issued (loads, staging), `turn()` between the
+    // last but one step and the last: the wait and barrier behind which the next stage's fragments may be read; the
+    // last step runs from registers, over the LDS latency of those.
+    auto stage_steps = [&](int xstage, int wstage, int xnext, auto &&work, auto &&turn) {
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int ks = st / AH, half = st % AH;
+            const bool last = st + 1 == STEPS;
+            work(st);
+            if (last) turn();
+            const bool next_b = half + 1 == AH;                    // the step after starts a new k-step
+            if (last) load_a(xnext, 0, 0, fa[(st + 1) & 1]);
+            else load_a(xstage, (st + 1) / AH, (st + 1) % AH, fa[(st + 1) & 1]);
+            if (next_b) {
+                if (last) load_b(wstage ^ 1, 0, fb[(ks + 1) & 1]);
+                else load_b(wstage, ks + 1, fb[(ks + 1) & 1]);
+            }
+            mfma_step(half, fa[st & 1], fb[ks & 1]);
+            spread(A_READS + (next_b ? B_READS : 0));
+            if constexpr (SYM) __builtin_amdgcn_sched_barrier(0);
+        }
     };
 
     constexpr int EXT_STEPS = 2;                                        // LoRA steps whose operands are prefetched
     constexpr int EXT_A = BM * 2 / NSTG, EXT_W = BN * 2 / NSTG;   // pieces per staging thread and LoRA step
     u16x8_t ext_a[EXT_STEPS][EXT_A], ext_w[EXT_STEPS][EXT_W];
 
+    // Where unit i of this thread lies in stage kt: weight row n and first column k0.  TRANS: 64 contraction rows n,
+    // BN/32 units across the output columns k; else BN output rows n, 2 units along the contraction k.
+    auto unit_row = [&](int kt, int i) {
+        const int u = stid + NSTG * i;
+        return TRANS ? (kt_first + kt) * BK + (u & 63) : col0 + (u >> 1);
+    };
+    auto unit_col = [&](int kt, int i) {
+        const int u = stid + NSTG * i;
+        return TRANS ? col0 + (u >> 6) * 32 : (kt_first + kt) * BK + (u & 1) * 32;
+    };
     // global -> registers for stage kt.  Branch-free: every address is clamped into the valid range and
     // whatever lies beyond the contraction length (or beyond the weight's rows / columns) is neutralised by a
-    // zero scale, so stages past the end may be fetched and staged harmlessly.
+    // zero scale, so stages past the end may be fetched and staged harmlessly.  Byte offsets fit 32 bits (the entry
+    // points accept fewer than 2^32 codes): a uniform base and one register per address.
+    const uint32_t row_bytes = (uint32_t)Kw * 4u;
+    const uint32_t g32_one = a.g32_magic ? 0u : ~0u;        // G == 32: the group is q itself (no branch in the loop)
     auto load_global = [&](int kt, Regs &rg) {
-        const int kbase = (kt_first + kt) * BK;
 #pragma unroll
         for (int i = 0; i < WU; ++i) {
-            const int u = stid + NSTG * i;
-            int n, k0;
-            bool ok;
-            if constexpr (TRANS) {          // 64 contraction rows n, BN/32 units across the output columns k
-                n = kbase + (u & 63);
-                k0 = col0 + (u >> 6) * 32;
-                ok = n < a.N && k0 < a.K;
-            } else {                        // BN output rows n, 2 units along the contraction k
-                n = col0 + (u >> 1);
-                k0 = kbase + (u & 1) * 32;
-                ok = k0 < a.K;
-            }
-            n = min(n, a.N - 1);
-            k0 = min(k0, a.K - 32);
-            load_unit<BITS>(a.packed + (long)n * Kw + (k0 >> 5) * BITS, rg.w[i]);
-            const long gi = (long)n * ng + (a.g32_magic ? (int)__umulhi((uint32_t)(k0 >> 5), a.g32_magic) : (k0 >> 5));
-            rg.s[i] = a.scales[gi];
-            rg.z[i] = a.zeros[gi];
-            rg.ok[i] = ok;
+            const uint32_t n = (uint32_t)min(unit_row(kt, i), a.N - 1), q = (uint32_t)min(unit_col(kt, i), a.K - 32) >> 5;
+            load_unit<BITS>((const uint32_t *)((const uint8_t *)a.packed + (n * row_bytes + q * (BITS * 4u))), rg.w[i]);
+            const uint32_t gi = n * (uint32_t)ng + (__umulhi(q, a.g32_magic) + (q & g32_one));
+            rg.s[i] = *(const uint16_t *)((const uint8_t *)a.scales + gi * 2u);
+            rg.z[i] = *(a.zeros + gi);
         }
     };
 
-    // registers -> LDS: every unit dequantised 8 codes at a time; parts p0 .. p1 of unit i
-    auto stage_parts = [&](const Regs &rg, int buf, int i, int p0, int p1) {
-        uint16_t *Bs = wsm + buf * WS;
+    // registers -> LDS: the units of stage kt, dequantised 8 codes at a time; parts p0 .. p1 of unit i.  A unit's four
+    // pieces go to slots that differ in their lower two bits only: piece p lies at (address of piece 0) ^ 16 p bytes.
+    auto stage_parts = [&](int kt, const Regs &rg, int buf, int i, int p0, int p1) {
         const int u = stid + NSTG * i;
         DequantConst<BITS, BF16> dq;
-        dq.set(rg.ok[i] ? f16_bits_to_f32(rg.s[i]) : 0.f, (float)rg.z[i]);
+        const bool ok = TRANS ? unit_row(kt, i) < a.N && unit_col(kt, i) < a.K : unit_col(kt, i) < a.K;
+        dq.set(ok ? f16_bits_to_f32(rg.s[i]) : 0.f, (float)rg.z[i]);
+        uint32_t at;                                // byte offset of piece 0 in the stage
+        if constexpr (TRANS) at = (u & 63) * (WPITCH * 2) + ((((u >> 6) * 4) ^ wswz(u & 63)) * 16);
+        else if constexpr (SYM) at = (u >> 1) * (WPITCH * 2) + ((((u & 1) * 4) ^ fswz(u >> 1)) * 16);   // row u / 2
+        else at = (u >> 1) * (WPITCH * 2) + (u & 1) * 64;
+        if constexpr (SYM) asm("" : "+v"(at));      // the four addresses are formed when needed: four registers fewer
+        uint8_t *Bs = (uint8_t *)(wsm + buf * WS);
 #pragma unroll
         for (int part = p0; part < p1; ++part) {
             const u16x8_t v = dequant8<BITS, BF16>(rg.w[i], part, dq);
-            if constexpr (TRANS) {
-                *(u16x8_t *)(Bs + (u & 63) * WPITCH + ((((u >> 6) * 4 + part) ^ wswz(u & 63)) * 8)) = v;
-            } else if constexpr (SYM) {        // row u / 2, pieces 4 (u % 2) + part
-                *(u16x8_t *)(Bs + (u >> 1) * WPITCH + ((((u & 1) * 4 + part) ^ fswz(u >> 1)) * 8)) = v;
-            } else {
-                *(u16x8_t *)(Bs + (u >> 1) * LDS_STRIDE + (u & 1) * 32 + part * 8) = v;
-            }
+            *(u16x8_t *)(Bs + (TRANS || SYM ? at ^ (uint32_t)(part * 16) : at + (uint32_t)(part * 16))) = v;
         }
     };
-    auto stage = [&](const Regs &rg, int buf) {
+    auto stage = [&](int kt, const Regs &rg, int buf) {
 #pragma unroll
-        for (int i = 0; i < WU; ++i) stage_parts(rg, buf, i, 0, 4);
+        for (int i = 0; i < WU; ++i) stage_parts(kt, rg, buf, i, 0, 4);
     };
 
     if constexpr (SYM) {
@@ -331,20 +386,11 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
             const uint32_t dst = xs_lds + (uint32_t)(stage * XS + (MW * i + cw) * 512) * 2u;
             dma16(a.act, xoff[i] + k2, (uint32_t)__builtin_amdgcn_readfirstlane((int)dst));
         };
-        // a k-step's MFMAs with the next fragments' LDS reads slotted between them (the dequantisation and its LDS
-        // writes are left to the compiler's own schedule: a hint that placed them too took minutes to compile)
-        auto spread = [&]() {
-#pragma unroll
-            for (int i = 0; i < MI * NI; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        // one MFMA
-                if (i < MI + (TRANS ? 2 * NI : NI)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-            }
-        };
         // Requests complete in the order they were made.  Per stage a wave first requests its weight units (at least
         // WL instructions), then the XDMA activation pieces for the stage after next; "the activation pieces of the
         // next stage have landed" is therefore "at most XDMA + WL requests are outstanding".
         constexpr int WL = WU * (BITS == 3 ? 3 : (BITS == 8 ? 2 : 1));
-        constexpr int NSETS = 3;
+        constexpr int NSETS = 2;
         Regs rs[NSETS];
 #pragma unroll
         for (int i = 0; i < NSETS; ++i) load_global(i, rs[i]);
@@ -352,46 +398,27 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         for (int i = 0; i < XDMA; ++i) issue_x(0, 0, i);
 #pragma unroll
         for (int i = 0; i < XDMA; ++i) issue_x(1, 1, i);
-        stage(rs[0], 0);
+        stage(0, rs[0], 0);
         load_global(NSETS, rs[0]);
         wait_vm_and_barrier<XDMA + WL>();       // activation stage 0 and every wave's share of weight stage 0 are in LDS
-        Frags f[2];
-        load_frags(0, 0, 0, f[0]);
+        load_a(0, 0, 0, fa[0]);
+        load_b(0, 0, fb[0]);
         int xstage = 0;
+        static_assert(STEPS == 8 && WU == 1 && XDMA == 4, "a part of the staging or a request per step");
         // stage kt: rg holds the units of stage kt + 1, and is refilled with those of stage kt + 1 + NSETS
         auto step = [&](int kt, Regs &rg) {
             const int wstage = kt & 1, wfill = wstage ^ 1;
             const int xnext = xstage + 1 == NXS ? 0 : xstage + 1;
             const int xfill = xnext + 1 == NXS ? 0 : xnext + 1;
-            auto issue_quarter = [&](int qtr) {
-#pragma unroll
-                for (int i = qtr * (XDMA / 4); i < (qtr + 1) * (XDMA / 4); ++i) issue_x(kt + 2, xfill, i);
+            auto work = [&](int st) {
+                if (st % 2 == 0) stage_parts(kt + 1, rg, wfill, 0, st / 2, st / 2 + 1);
+                else issue_x(kt + 2, xfill, st / 2);
             };
-            auto stage_quarter = [&](int qtr) {      // WU parts: quarter 4 i / WU + .. of unit i
-                stage_parts(rg, wfill, qtr * WU / 4, (qtr * WU) % 4, (qtr * WU) % 4 + WU);
+            auto turn = [&]() {
+                wait_vm_and_barrier<XDMA + WL>();    // activation stage kt + 1 has landed; weight stage kt + 1 is written
+                load_global(kt + 1 + NSETS, rg);
             };
-            load_frags(xstage, wstage, 1, f[1]);
-            stage_quarter(0);
-            mfma_frags(f[0]);
-            spread();
-            issue_quarter(0);
-            load_frags(xstage, wstage, 2, f[0]);
-            stage_quarter(1);
-            mfma_frags(f[1]);
-            spread();
-            issue_quarter(1);
-            load_frags(xstage, wstage, 3, f[1]);
-            stage_quarter(2);
-            mfma_frags(f[0]);
-            spread();
-            issue_quarter(2);
-            stage_quarter(3);
-            issue_quarter(3);
-            wait_vm_and_barrier<XDMA + WL>();   // activation stage kt + 1 has landed; weight stage kt + 1 is written
-            load_global(kt + 1 + NSETS, rg);
-            load_frags(xnext, wfill, 0, f[0]);
-            mfma_frags(f[1]);
-            spread();
+            stage_steps(xstage, wstage, xnext, work, turn);
             xstage = xnext;
         };
         int kt0 = 0;
@@ -421,18 +448,6 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
             const uint32_t dst = xs_lds + (uint32_t)(stage * XS + (MW * i + cw) * 512) * 2u;   // wave-uniform byte address
             dma16(a.act, xoff[i] + k2, (uint32_t)__builtin_amdgcn_readfirstlane((int)dst));
         };
-        // One k-step: the fragments of a later k-step are requested from LDS while the MFMAs of the current one
-        // issue, one LDS read slotted behind each MFMA so the matrix pipe never waits on a burst of reads.
-        auto kstep = [&](int xstage, int wstage, int rks, Frags &into, const Frags &use) {
-            load_frags(xstage, wstage, rks, into);
-            mfma_frags(use);
-#pragma unroll
-            for (int i = 0; i < MI * NI; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        // one MFMA
-                if (i < MI + (TRANS ? 2 * NI : NI)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-            }
-        };
-
 #pragma unroll
         for (int i = 0; i < XDMA; ++i) issue_x(0, 0, i);
         if constexpr (NXS == 3) {
@@ -441,28 +456,19 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         }
         constexpr int AHEAD = NXS == 3 ? XDMA : 0;   // loads that may still be in flight when a stage is needed
         wait_vm_and_barrier<AHEAD>();           // stage 0 of the activations has landed; weights staged by waves 4-7
-        Frags f[2];
-        load_frags(0, 0, 0, f[0]);
+        load_a(0, 0, 0, fa[0]);
+        load_b(0, 0, fb[0]);
         int xstage = 0;                         // kt % NXS
         for (int kt = 0; kt < KT; ++kt) {
-            const int wstage = kt & 1;
             const int xnext = xstage + 1 == NXS ? 0 : xstage + 1;
             const int xfill = NXS == 3 ? (xnext + 1 == NXS ? 0 : xnext + 1) : xnext;   // the stage NXS-1 ahead
-            // the last k-step of a stage runs from registers after the barrier, overlapping the LDS latency of the
-            // next stage's first fragments; the activation loads for stage kt+2 are spread over the k-steps
-            auto issue_quarter = [&](int qtr) {
+            // the activation loads for stage kt+2 are spread over the steps
+            auto work = [&](int st) {
 #pragma unroll
-                for (int i = qtr * (XDMA / 4); i < (qtr + 1) * (XDMA / 4); ++i) issue_x(kt + NXS - 1, xfill, i);
+                for (int i = st * XDMA / STEPS; i < (st + 1) * XDMA / STEPS; ++i) issue_x(kt + NXS - 1, xfill, i);
             };
-            issue_quarter(0);
-            kstep(xstage, wstage, 1, f[1], f[0]);
-            issue_quarter(1);
-            kstep(xstage, wstage, 2, f[0], f[1]);
-            issue_quarter(2);
-            kstep(xstage, wstage, 3, f[1], f[0]);
-            issue_quarter(3);
-            wait_vm_and_barrier<AHEAD>();       // stage kt+1 has landed (only loads for a later stage may be pending)
-            kstep(xnext, wstage ^ 1, 0, f[0], f[1]);
+            auto turn = [&]() { wait_vm_and_barrier<AHEAD>(); };   // stage kt+1 has landed (only loads for a later one may be pending)
+            stage_steps(xstage, kt & 1, xnext, work, turn);
             xstage = xnext;
         }
         wait_vm_and_barrier<0>();               // the loads issued past the last stage have landed: LDS is quiet
@@ -501,11 +507,11 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         Regs rs[NSETS];
 #pragma unroll
         for (int i = 0; i < NSETS; ++i) load_global(i, rs[i]);
-        stage(rs[0], 0);
+        stage(0, rs[0], 0);
         load_global(NSETS, rs[0]);
         __syncthreads();
         auto step = [&](int kt, Regs &rg) {
-            stage(rg, (kt + 1) & 1);
+            stage(kt + 1, rg, (kt + 1) & 1);
             load_global(kt + 1 + NSETS, rg);
             __syncthreads();
         };
@@ -522,7 +528,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         __syncthreads();                        // pairs with the MFMA waves' final wait-and-barrier
     }
 
-    // --- LoRA term as extra contraction steps: Act' = sc * t (or u), W' = B (or A^T), zero-padded to 16.
+    // --- LoRA term as extra contraction steps: Act' = sc * t (or u), W' = B (or A^T), zero-padded to 32.
     //     Every wave is past the last barrier of the main loop, so every LDS stage is free.
     constexpr int ESTR = TN + 8;                            // row pitch of a wave's epilogue area
     constexpr int SIDE_R = 32;                              // adapter columns of the masked epilogue's side tiles
@@ -546,11 +552,10 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         }
     }
     if (!MASKED && a.r > 0 && split == 0) {                 // the first workgroup of a split contraction adds it
-        const int nsteps = (a.r + 15) / 16, width = nsteps * 16;
-        if (!SYM && stager && nsteps <= EXT_STEPS) {        // operands already in registers
+        const int nsteps = (a.r + 31) / 32, width = nsteps * 32;
+        if (!SYM && stager && nsteps == 1) {                // operands already in registers (zero past the rank)
 #pragma unroll
             for (int st = 0; st < EXT_STEPS; ++st) {
-                if (st >= nsteps) break;
 #pragma unroll
                 for (int i = 0; i < EXT_A; ++i) {
                     const int c = stid + NSTG * i, r = c >> 1, jc = 2 * st + (c & 1);
@@ -603,9 +608,12 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         __syncthreads();
         if (feeder) {
             for (int ks = 0; ks < nsteps; ++ks) {
-                Frags fx;
-                load_frags(0, 0, ks, fx);
-                mfma_frags(fx);
+                load_b(0, ks, fb[0]);
+#pragma unroll
+                for (int half = 0; half < AH; ++half) {
+                    load_a(0, ks, half, fa[0]);
+                    mfma_step(half, fa[0], fb[0]);
+                }
             }
         }
         __syncthreads();
@@ -614,21 +622,17 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     // --- epilogue: fp32 accumulators -> 16 bit.  Each MFMA wave lays its TM x TN block into its own LDS area in
     //     row-major order; then all waves stream the areas out in 16-byte pieces (8 lanes per 128-byte row
     //     segment).  Rows beyond M and columns beyond NO (always whole 8-element pieces) are dropped.
-    if (a.splits > 1) {
-        // split contraction: the fp32 accumulators go to this split's plane as they are (a lane's 32 neighbours
-        // write 128 consecutive bytes of a row); a second kernel sums the planes in order and rounds once
+    if (!SYM && a.splits > 1) {
+        // split contraction: the fp32 accumulators go to this split's plane as they are (16 bytes per lane,
+        // 64 consecutive bytes of a row); a second kernel sums the planes in order and rounds once
         if (feeder) {
             float *P = a.part + (size_t)split * a.M * NO;
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
-                    const int gcol = col0 + wn * TN + j * 32 + (lane & 31);
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int grow = row0 + wm * TM + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-                        if (grow < a.M && gcol < NO) P[(size_t)grow * NO + gcol] = acc[i][j][v];
-                    }
+                    const int grow = row0 + wm * TM + i * 16 + (lane & 15), gcol = col0 + wn * TN + j * 16 + (lane >> 4) * 4;
+                    if (grow < a.M && gcol < NO) *(float4_t *)(P + (size_t)grow * NO + gcol) = acc[i][j];   // NO % 8 == 0
                 }
         }
         return;
@@ -638,11 +642,11 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    E[(i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)) * ESTR + j * 32 + (lane & 31)] =
-                        to16<BF16>(acc[i][j][v]);
+            for (int j = 0; j < NI; ++j) {
+                const u16x4_t h = {to16<BF16>(acc[i][j][0]), to16<BF16>(acc[i][j][1]), to16<BF16>(acc[i][j][2]),
+                                   to16<BF16>(acc[i][j][3])};
+                *(u16x4_t *)(E + (i * 16 + (lane & 15)) * ESTR + j * 16 + (lane >> 4) * 4) = h;
+            }
     }
     __syncthreads();
     {
