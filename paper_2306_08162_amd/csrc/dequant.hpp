@@ -7,8 +7,11 @@
 //
 // fp16: a code is dropped into the mantissa of the constant 1024.0 (bits 0x6400), giving 1024 + c * 2^p exactly
 // for a code sitting at bit p of a 16-bit lane; one packed fma with (2^-p, -(1024 * 2^-p + z)) yields the exact
-// small integer c - z, and one packed multiply applies the scale.  bf16: there is no packed bf16 arithmetic, so
-// codes go through fp32 (fma(c, s, -z s)) and are packed with the hardware bf16 conversion.
+// small integer c - z, and one packed multiply applies the scale.  bf16: there is no packed bf16 arithmetic.  The
+// same fp16 values 1024 + c * 2^p (fp32 holds their products with a scale exactly: 11 bits each) go through one
+// mixed-precision fma per code, (1024 + c * 2^p) * (s * 2^-p) - (1024 * 2^-p + z) * s = s (c - z) exactly, and are packed
+// with the hardware bf16 conversion: 2.0 to 3.0 instructions per code where extracting and converting every code by
+// itself took 2.5 to 3.4.
 #pragma once
 #include "common.hpp"
 
@@ -39,11 +42,17 @@ struct DequantConst<BITS, false> {
 
 template <int BITS>
 struct DequantConst<BITS, true> {
-    float s, nzs;      // scale and -z * s
+    // codes sit at bit p = STEP i of a 16-bit lane, i < NP
+    static constexpr int NP = BITS == 2 ? 4 : (BITS == 8 ? 1 : 2), STEP = BITS;
+    float mul[NP], off[NP];     // s * 2^-p and -(1024 * 2^-p + z) * s
     __device__ __forceinline__ void set(float sc, float z)
     {
-        s = sc;
-        nzs = -z * sc;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const float inv = 1.f / (float)(1 << (STEP * i));
+            mul[i] = sc * inv;
+            off[i] = -(1024.f * inv + z) * sc;
+        }
     }
 };
 
@@ -113,35 +122,34 @@ __device__ __forceinline__ u16x8_t dequant8(const uint32_t (&w)[BITS], int part,
                 out[i] = fp16_pair<SCALE>(spread_byte(x >> (6 * i), 0) & (0x00380007u | MAGIC), mul, c.off[0], c.s2);
         }
     } else {
-        constexpr uint32_t mask = (1u << BITS) - 1u;
-        uint32_t x;
-        int base;                                  // bit offset of code 8*part inside x
-        if constexpr (BITS == 3) {
-            x = window<BITS>(w, 24 * part);
-            base = 0;
-        } else if constexpr (BITS == 8) {
-            x = 0;
-            base = 0;
-        } else {
-            x = w[(8 * part * BITS) >> 5];
-            base = (8 * part * BITS) & 31;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float f[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int e = 2 * i + h;
-                uint32_t q;
-                if constexpr (BITS == 8)
-                    q = (w[2 * part + (e >> 2)] >> (8 * (e & 3))) & 0xffu;
-                else
-                    q = (x >> (base + BITS * e)) & mask;
-                f[h] = (float)q * c.s + c.nzs;
-            }
+        constexpr uint32_t MAGIC = 0x64006400u;
+        // two neighbouring codes as (1024 + c * 2^p, 1024 + c' * 2^p'), p and p' given by their index into c.mul
+        auto pair = [&](uint32_t bits, int p0, int p1) {
             typedef float float2_t __attribute__((ext_vector_type(2)));
             typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-            out[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{f[0], f[1]}, bf16x2_t));
+            const half2_t h = __builtin_bit_cast(half2_t, bits);
+            const float2_t f = {__builtin_fmaf((float)h[0], c.mul[p0], c.off[p0]),
+                                __builtin_fmaf((float)h[1], c.mul[p1], c.off[p1])};
+            return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+        };
+        if constexpr (BITS == 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[i] = pair(spread_byte(w[part], i) & (0x00F0000Fu | MAGIC), 0, 1);
+        } else if constexpr (BITS == 2) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint32_t p = spread_byte(w[part >> 1], 2 * (part & 1) + i);
+                out[2 * i] = pair(p & (0x000C0003u | MAGIC), 0, 1);
+                out[2 * i + 1] = pair(p & (0x00C00030u | MAGIC), 2, 3);
+            }
+        } else if constexpr (BITS == 8) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out[i] = pair(__builtin_amdgcn_perm(MAGIC, w[2 * part + (i >> 1)], (i & 1) ? 0x05030502u : 0x05010500u), 0, 0);
+        } else {
+            const uint32_t x = window<BITS>(w, 24 * part);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[i] = pair(spread_byte(x >> (6 * i), 0) & (0x00380007u | MAGIC), 0, 1);
         }
     }
     return __builtin_bit_cast(u16x8_t, out);
