@@ -318,6 +318,7 @@ void launch_fwd_staged(const FwdMulti &m, int rg, hipStream_t s)
 }  // namespace qlora
 
 #include "gemv_fwd_m16.hpp"
+#include "gemv_fwd_wave.hpp"
 
 namespace qlora {
 
@@ -327,6 +328,7 @@ template <int BITS, bool BF16>
 bool launch_fwd_mb(const FwdMulti &m, int rg, hipStream_t s)
 {
     const bool zpacked = m.p[0].zpacked != nullptr;       // only the kernel with staged group constants reads those
+    if (launch_fwd_wave<BITS, BF16>(m, rg, s)) return true;
     if (launch_fwd_m16<BITS, BF16>(m, rg, s)) return true;
     if (zpacked) return false;
     if (m.p[0].M <= 16) {

@@ -5,7 +5,7 @@
 // through, not the bytes: a lane that fetches its own MFMA fragment of a 2-bit weight touches 8 bytes of a row, so a
 // wave instruction brings in sixteen 32-byte pieces, and the group constants cost two more such instructions per
 // fragment.  Here nothing is fetched fragment-wise.  A workgroup of eight waves owns 16 NB weight rows and walks K in
-// stages of 8 KS columns (KS = 128; 64 for 8-bit codes, for two token blocks and for 32 adapter rows): per stage the
+// stages of 8 KS columns (KS = 64): per stage the
 // packed words of all its rows (row segments of KS BITS bytes, whole cache lines), the token rows of x (16 or 32; only
 // the requests that hold rows below M are made) and the adapter rows of A arrive by direct-to-LDS loads of 1 KB per
 // instruction, two stages in flight, and every wave takes the fragments of its KS contraction indices from LDS.  The
@@ -22,14 +22,9 @@ namespace {
 
 constexpr int M16_NW = 8;                  // waves of a workgroup; wave w owns columns KS w .. KS w + KS of a stage
 constexpr int M16_LDS = 160 * 1024;
-// Columns of a wave per stage and stages in LDS.  8-bit codes: half the columns, so that three blocks of weight rows
-// fit beside the activations, and three stages (one barrier per stage instead of two).  The narrower widths are
-// faster with the wide slices (INT2 gate/up at M = 16: 12.0 against 13.3 us).
-// With two 16-row token blocks (mb = 2: 17 to 32 token rows) the slices are 64 columns wide for every code width, so
-// that 32 rows of x per wave fit, and there are two stages.
-// The same narrow slices when 32 rows of A ride along (ranks 17 to 32).
-constexpr int m16_ks(int bits, int mb, int ar) { return bits == 8 || mb == 2 || ar == 32 ? 64 : 128; }
-constexpr int m16_nst(int bits, int mb, int ar) { return bits == 8 && mb == 1 && ar <= 16 ? 3 : 2; }
+// Columns of a wave per stage and stages in LDS: 64 columns, so that 32 rows of x or of A per wave fit, and two stages.
+constexpr int m16_ks(int, int, int) { return 64; }
+constexpr int m16_nst(int, int, int) { return 2; }
 
 // slot of the 16-byte piece `piece` of weight row n inside the row's stage segment of PPR pieces (its own inverse)
 template <int BITS, int PPR>
@@ -400,18 +395,18 @@ void launch_fwd_m16_nb(const FwdMulti &m, int nb, hipStream_t s)
     }
 }
 
-// Serves the call if its shape allows: up to 32 token rows (above 16, or with more than 16 adapter rows: not for 3-bit
-// codes), K and the group size
-// multiples of 128 (a wave's columns of a stage then share their group constants), t either computed here from at most
-// 32 adapter rows or handed in, and room in LDS for the stages of at least two 16-row blocks (one block would pull x
-// through every compute unit once per 16 weight rows).
+// Serves the call if its shape allows: 17 to 32 token rows, or up to 16 with 17 to 32 adapter rows (fewer: gemv_fwd_wave.hpp);
+// not 3-bit codes; K and the group size multiples of 128 (a wave's columns of a stage then share their group constants), t
+// either computed here from at most 32 adapter rows or handed in, and room in LDS for the stages of at least two 16-row
+// blocks (one block would pull x through every compute unit once per 16 weight rows).
 template <int BITS, bool BF16>
 bool launch_fwd_m16(const FwdMulti &m, int rg, hipStream_t s)
 {
     const FwdArgs &a = m.p[0];
     if (a.M > 32 || a.K % 128 != 0 || (a.K / a.ng) % 128 != 0 || rg > 2 || (rg == 0 && a.r > 64)) return false;
     const int mb = a.M > 16 ? 2 : 1;
-    if (BITS == 3 && (mb == 2 || rg == 2)) return false;   // 64-column slices would cut the 12-byte units of 3-bit codes
+    if (BITS == 3) return false;                           // 64-column slices would cut the 12-byte units of 3-bit codes
+    if (mb == 1 && rg < 2) return false;                   // gemv_fwd_wave.hpp
     for (int i = 0; i < m.count; ++i) {
         const FwdArgs &b = m.p[i];            // 16-byte requests: aligned arrays, constants in whole pieces
         const uintptr_t bits_or = (uintptr_t)b.x | (uintptr_t)b.packed | (uintptr_t)b.scales | (uintptr_t)b.zeros |
@@ -438,20 +433,16 @@ bool launch_fwd_m16(const FwdMulti &m, int rg, hipStream_t s)
         return true;
     }
     if (nb == 0) nb = nb_max;
-    if (mb == 1) {
-        switch (ar) {
-        case 0: launch_fwd_m16_nb<BITS, BF16, 0, 1>(m, nb, s); break;
-        case 8: launch_fwd_m16_nb<BITS, BF16, 8, 1>(m, nb, s); break;
-        case 16: launch_fwd_m16_nb<BITS, BF16, 16, 1>(m, nb, s); break;
-        default:
-            if constexpr (BITS != 3) launch_fwd_m16_nb<BITS, BF16, 32, 1>(m, nb, s);
-        }
-    } else if constexpr (BITS != 3) {
-        switch (ar) {
-        case 0: launch_fwd_m16_nb<BITS, BF16, 0, 2>(m, nb, s); break;
-        case 8: launch_fwd_m16_nb<BITS, BF16, 8, 2>(m, nb, s); break;
-        case 16: launch_fwd_m16_nb<BITS, BF16, 16, 2>(m, nb, s); break;
-        default: launch_fwd_m16_nb<BITS, BF16, 32, 2>(m, nb, s); break;
+    if constexpr (BITS != 3) {
+        if (mb == 1) {
+            launch_fwd_m16_nb<BITS, BF16, 32, 1>(m, nb, s);
+        } else {
+            switch (ar) {
+            case 0: launch_fwd_m16_nb<BITS, BF16, 0, 2>(m, nb, s); break;
+            case 8: launch_fwd_m16_nb<BITS, BF16, 8, 2>(m, nb, s); break;
+            case 16: launch_fwd_m16_nb<BITS, BF16, 16, 2>(m, nb, s); break;
+            default: launch_fwd_m16_nb<BITS, BF16, 32, 2>(m, nb, s); break;
+            }
         }
     }
     return true;
