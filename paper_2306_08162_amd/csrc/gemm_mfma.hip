@@ -139,6 +139,9 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     constexpr int MH = SYM ? 2 : 4, AH = MI / MH;
     static_assert(MI % MH == 0, "a stage is made of whole steps of MH x NI MFMAs");
     constexpr int STEPS = AH * BK / 32;             // such steps per stage
+    // The symmetric bf16 backward kernel holds its addresses and group constants for one use only and dequantises behind a
+    // step's MFMAs: 5 to 23 registers spilled otherwise (4096 x 4096 x 4096, INT2: 167 us against 140)
+    constexpr bool TIGHT = SYM && BF16 && TRANS;
     constexpr int XDMA = BM / 8 / MW;               // direct-to-LDS loads per MFMA wave per stage (8 rows each)
     static_assert(XDMA >= 4 && XDMA % 4 == 0, "loads are spread over the four k-steps");
     constexpr int WU = 2 * BN / NSTG;               // 32-code weight units per staging thread per stage
@@ -241,7 +244,9 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         static_assert(!TRANS || TN == 64, "the pieces of a wave's block columns differ in slot bits 1 and 2 only");
     }
     auto load_a = [&](int xstage, int ks, int half, AFrags &f) {
-        const uint16_t *As = xs + xstage * XS + aoff[ks] + half * MH * 16 * BK;
+        int at = aoff[ks];
+        if constexpr (TIGHT) asm volatile("" : "+v"(at));
+        const uint16_t *As = xs + xstage * XS + at + half * MH * 16 * BK;
 #pragma unroll
         for (int i = 0; i < MH; ++i) f.a[i] = *(const u16x8_t *)(As + i * 16 * BK);
     };
@@ -298,7 +303,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         for (int st = 0; st < STEPS; ++st) {
             const int ks = st / AH, half = st % AH;
             const bool last = st + 1 == STEPS;
-            work(st);
+            if (!TIGHT || last) work(st);
             if (last) turn();
             const bool next_b = half + 1 == AH;                    // the step after starts a new k-step
             if (last) load_a(xnext, 0, 0, fa[(st + 1) & 1]);
@@ -308,6 +313,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                 else load_b(wstage, ks + 1, fb[(ks + 1) & 1]);
             }
             mfma_step(half, fa[st & 1], fb[ks & 1]);
+            if (TIGHT && !last) work(st);
             spread(A_READS + (next_b ? B_READS : 0));
             if constexpr (SYM) __builtin_amdgcn_sched_barrier(0);
         }
@@ -350,7 +356,9 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         const int u = stid + NSTG * i;
         DequantConst<BITS, BF16> dq;
         const bool ok = TRANS ? unit_row(kt, i) < a.N && unit_col(kt, i) < a.K : unit_col(kt, i) < a.K;
-        dq.set(ok ? f16_bits_to_f32(rg.s[i]) : 0.f, (float)rg.z[i]);
+        uint32_t sr = rg.s[i], zr = rg.z[i];
+        if constexpr (TIGHT) asm volatile("" : "+v"(sr), "+v"(zr));      // not kept from one part to the next
+        dq.set(ok ? f16_bits_to_f32((uint16_t)sr) : 0.f, (float)zr);
         uint32_t at;                                // byte offset of piece 0 in the stage
         if constexpr (TRANS) at = (u & 63) * (WPITCH * 2) + ((((u >> 6) * 4) ^ wswz(u & 63)) * 16);
         else if constexpr (SYM) at = (u >> 1) * (WPITCH * 2) + ((((u & 1) * 4) ^ fswz(u >> 1)) * 16);   // row u / 2
