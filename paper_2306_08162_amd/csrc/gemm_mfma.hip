@@ -511,7 +511,9 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         }
         // stage kt+1 is written while the MFMA waves work on stage kt; NSETS later stages are in flight from
         // memory (one register set each)
-        constexpr int NSETS = 3;
+        // (forward with 128-row tiles, whose stages are half as long, gains 1 to 2 % from a fourth set; backward loses 2 to 4 %
+        // where the contraction is split)
+        constexpr int NSETS = BM == 128 && !TRANS ? 4 : 3;
         Regs rs[NSETS];
 #pragma unroll
         for (int i = 0; i < NSETS; ++i) load_global(i, rs[i]);
@@ -743,10 +745,12 @@ void launch_tiles(GemmArgs &a, hipStream_t s)
     a.tiles_n = (NO + BN - 1) / BN;
     a.splits = 1;
     a.kt_split = (KC + BK - 1) / BK;
-    // fewer tiles than CUs: halve the tile height, so that (up to) twice as many CUs work; far fewer: also split
-    // the contraction over several workgroups per tile
+    // 128-row tiles while they are one round of the 256 CUs (a CU holds one workgroup), and if they are far fewer also the
+    // contraction split over several workgroups per tile.  A round of 128-row tiles takes 0.6 times as long as one of
+    // 256-row tiles (4096 x 4096, INT4, fp16: 39 and 64 us forward, 42 and 66 backward), so two rounds of them lose to one:
+    // M = 1397, 4096 x 4096, bf16 INT4 (352 tiles of 128 rows or 192 of 256) 79 -> 52 us forward, 76 -> 56 backward.
     if constexpr (BM == 256) {
-        if (((a.M + 255) / 256) * a.tiles_n < 256) {
+        if (((a.M + 127) / 128) * a.tiles_n <= 256) {
             a.tiles_m = (a.M + 127) / 128;
             if constexpr (TRANS) {
                 if (a.keep) {           // the masked epilogue needs the whole contraction in one workgroup

@@ -19,12 +19,17 @@ namespace {
 
 constexpr int FW_NW = 8;                   // waves of a workgroup; wave w takes the chunks w, w + 8, ... of its columns
 constexpr int FW_LDS = 160 * 1024;
-// columns of a chunk (8-bit codes of several blocks: half, so that two chunks fit)
-constexpr int fw_ks(int bits, int nb) { return bits == 8 && nb > 1 ? 64 : 128; }
-constexpr int fw_xr(int bits, int nb, int xr) { return xr * fw_ks(bits, nb) < 512 ? 512 / fw_ks(bits, nb) : xr; }   // whole requests
+// columns of a chunk; half as many, so that two chunks fit, for 8-bit codes of several blocks and for 16 token rows beside 16
+// adapter rows (not for 3-bit codes: 64 columns of a row are no whole 16-byte pieces)
+constexpr int fw_ks(int bits, int nb, int ar, int xr)
+{
+    return bits != 3 && ((bits == 8 && nb > 1) || (ar == 16 && xr == 16)) ? 64 : 128;
+}
+constexpr int fw_xr(int ks, int xr) { return xr * ks < 512 ? 512 / ks : xr; }       // whole requests
 constexpr int fw_chunk(int bits, int nb, int ar, int xr)
 {
-    return (fw_xr(bits, nb, xr) + ar) * 2 * fw_ks(bits, nb) + nb * 16 * fw_ks(bits, nb) * bits / 8;
+    const int ks = fw_ks(bits, nb, ar, xr);
+    return (fw_xr(ks, xr) + ar) * 2 * ks + nb * 16 * ks * bits / 8;
 }
 constexpr int fw_tc(int ar) { return ar > 0 ? 16 : 64; }                                        // columns of t kept
 constexpr int fw_static(int ar) { return 16 * (fw_tc(ar) + 1) * 4; }
@@ -32,11 +37,12 @@ constexpr int fw_static(int ar) { return 16 * (fw_tc(ar) + 1) * 4; }
 constexpr int FW_RS = 20;
 constexpr int fw_red(int nb) { return FW_NW * (nb + 1) * 16 * FW_RS * 4; }
 
-// chunks of a wave in flight: as many as fit beside tables of up to 12 KB, four at most
+// chunks of a wave in flight: as many as fit beside tables of up to 12 KB (6 KB if that leaves only one), four at most
 constexpr int fw_depth(int bits, int nb, int ar, int xr)
 {
-    const int d = (FW_LDS - 12 * 1024 - fw_static(ar)) / (FW_NW * fw_chunk(bits, nb, ar, xr));
-    return d > 4 ? 4 : d;
+    const int chunks = FW_NW * fw_chunk(bits, nb, ar, xr), room = FW_LDS - fw_static(ar);
+    const int d = (room - 12 * 1024) / chunks;
+    return d > 4 ? 4 : (d >= 2 ? d : (room - 6 * 1024) / chunks);
 }
 
 // slot of the 16-byte piece `piece` of weight row n inside the row's PPR pieces of a chunk (its own inverse)
@@ -140,10 +146,10 @@ template <int BITS, bool BF16, int NB, int GR, int AR, int XMIN>
 __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int wg)
 {
     constexpr int NW = FW_NW, NT = NW * 64, R = 16 * NB, RT = R * GR;
-    constexpr int KS = fw_ks(BITS, NB), SS = KS / 32, UB = KS * BITS / 32;      // MFMA steps; bytes of a lane's codes
+    constexpr int KS = fw_ks(BITS, NB, AR, XMIN), SS = KS / 32, UB = KS * BITS / 32;      // MFMA steps; bytes of a lane's codes
     constexpr int PPR = KS * BITS / 128;                                    // pieces of a weight row per chunk
     constexpr int PR = KS / 8, RPI = 64 / PR;                               // pieces of an activation row; rows per request
-    constexpr int XR = fw_xr(BITS, NB, XMIN);
+    constexpr int XR = fw_xr(KS, XMIN);
     constexpr int CHUNK = fw_chunk(BITS, NB, AR, XMIN), D = fw_depth(BITS, NB, AR, XMIN);
     constexpr int WI = (R * PPR + 63) / 64, XI = XR / RPI, AI = AR / RPI;   // requests of a chunk
     constexpr int RQ = WI + XI + AI, RQ1 = WI + XI;                         // of the first group, of a later one
@@ -299,10 +305,15 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
                     for (int h = 0; h < 4; ++h) w[nb][h] = v[h];
 #pragma unroll
                     for (int h = 4; h < BITS; ++h) w[nb][h] = 0u;
-                } else {
+                } else if constexpr (UB == 8) {
                     const u32x2_t v = *(const u32x2_t *)(rowp + fw_slot<BITS, PPR>(n, q >> 1) * 16 + (q & 1) * 8);
                     w[nb][0] = v[0];
                     w[nb][1] = v[1];
+#pragma unroll
+                    for (int h = 2; h < BITS; ++h) w[nb][h] = 0u;
+                } else {
+                    w[nb][0] = *(const uint32_t *)(rowp + q * 4);
+                    w[nb][1] = 0u;
                 }
                 sc[nb] = *(const half_t *)((const uint8_t *)sct + (s_at + (uint32_t)(g * NB + nb) * 16u * s_row));
                 // one byte read for both storage forms of the zero-points, no branch: a branch per block would wait for its
