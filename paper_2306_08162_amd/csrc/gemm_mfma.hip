@@ -15,8 +15,9 @@
 // register-resident loop on random fp16 operands sustains 1590 TFLOP/s with 32x32x16 MFMAs and 1870 with 16x16x32 (half
 // the accumulator traffic per flop; bf16 1770 and 2015).  The 16x16x32 form, weights as the first operand and the MFMAs
 // of a step in serpentine order take the fp16 step at 2048 x 4096 x 4096, INT4, from 153 to 144 us, 4096 x 11008 -> 4096,
-// INT3, from 725 to 679 us and the bf16 forward pass at 8192 x 4096 -> 11008 from 725 to 693 us; launches of 128-row
-// tiles, which are too short to be held back by power, take the same time as before.
+// INT3, from 725 to 679 us and the bf16 forward pass at 8192 x 4096 -> 11008 from 725 to 693 us.  Launches of 128-row
+// tiles are not held back by power: against 32x32x16 MFMAs, activations first, they take 0 to 9 % less in bf16 and in the
+// forward pass, and between 2 % less and 2 % more in the fp16 backward pass.
 // Launches that give every compute unit at least one 256 x 256 tile use a second arrangement of the same parts
 // (SYM below): eight waves that each stage, load and multiply an eighth.
 #include "common.hpp"
@@ -93,6 +94,7 @@ struct StageRegs {
     uint32_t w[WU][BITS];
     uint16_t s[WU];     // raw fp16 bits: nothing may touch loaded values before they are staged, or the
     uint8_t z[WU];      // in-order memory counter would make that instruction wait for every load issued so far
+    bool ok[WU];        // (not SYM) false: the unit lies outside the weight, stage zeros
 };
 
 // wait until at most N vector-memory operations of this wave are outstanding, then meet the workgroup
@@ -274,13 +276,14 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     // The weight is the MFMA's first operand: a lane then holds four neighbouring output columns of one token row.  The
     // order of a step's MFMAs is a serpentine, so that each shares one operand with the one before: what the matrix
     // pipe draws, and with it the clock, follows how many operand bits change (register-resident loop on random fp16
-    // operands: 1835 TFLOP/s in plain order, 1934 as a serpentine).
+    // operands: 1835 TFLOP/s in plain order, 1934 as a serpentine).  Launches of 128-row tiles are not held back by power, and
+    // in plain order a step's first MFMAs need the fragments that arrive first (backward pass 2 % faster than as a serpentine).
     auto mfma_step = [&](int half, const AFrags &fa, const BFrags &fb) {
 #pragma unroll
         for (int i = 0; i < MH; ++i)
 #pragma unroll
             for (int jj = 0; jj < NI; ++jj) {
-                const int j = (i & 1) ? NI - 1 - jj : jj;
+                const int j = BM > 128 && (i & 1) ? NI - 1 - jj : jj;
                 acc[half * MH + i][j] = mfma16<BF16>(fb.b[j], fa.a[i], acc[half * MH + i][j]);
             }
     };
@@ -335,18 +338,31 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     };
     // global -> registers for stage kt.  Branch-free: every address is clamped into the valid range and
     // whatever lies beyond the contraction length (or beyond the weight's rows / columns) is neutralised by a
-    // zero scale, so stages past the end may be fetched and staged harmlessly.  Byte offsets fit 32 bits (the entry
-    // points accept fewer than 2^32 codes): a uniform base and one register per address.
+    // zero scale, so stages past the end may be fetched and staged harmlessly.  SYM: a uniform base and one register per
+    // address (byte offsets fit 32 bits: the entry points accept fewer than 2^32 codes), because registers are short.  The
+    // staging waves have registers to spare and form plain pointers: with the 32-bit form a launch of 128-row tiles took 3 to
+    // 9 % longer (513 x 4096 <- 11008, INT3, fp16, backward pass 118 -> 126 us).
     const uint32_t row_bytes = (uint32_t)Kw * 4u;
     const uint32_t g32_one = a.g32_magic ? 0u : ~0u;        // G == 32: the group is q itself (no branch in the loop)
     auto load_global = [&](int kt, Regs &rg) {
 #pragma unroll
         for (int i = 0; i < WU; ++i) {
-            const uint32_t n = (uint32_t)min(unit_row(kt, i), a.N - 1), q = (uint32_t)min(unit_col(kt, i), a.K - 32) >> 5;
-            load_unit<BITS>((const uint32_t *)((const uint8_t *)a.packed + (n * row_bytes + q * (BITS * 4u))), rg.w[i]);
-            const uint32_t gi = n * (uint32_t)ng + (__umulhi(q, a.g32_magic) + (q & g32_one));
-            rg.s[i] = *(const uint16_t *)((const uint8_t *)a.scales + gi * 2u);
-            rg.z[i] = *(a.zeros + gi);
+            if constexpr (SYM) {
+                const uint32_t n = (uint32_t)min(unit_row(kt, i), a.N - 1), q = (uint32_t)min(unit_col(kt, i), a.K - 32) >> 5;
+                load_unit<BITS>((const uint32_t *)((const uint8_t *)a.packed + (n * row_bytes + q * (BITS * 4u))), rg.w[i]);
+                const uint32_t gi = n * (uint32_t)ng + (__umulhi(q, a.g32_magic) + (q & g32_one));
+                rg.s[i] = *(const uint16_t *)((const uint8_t *)a.scales + gi * 2u);
+                rg.z[i] = *(a.zeros + gi);
+            } else {
+                int n = unit_row(kt, i), k0 = unit_col(kt, i);
+                rg.ok[i] = TRANS ? n < a.N && k0 < a.K : k0 < a.K;
+                n = min(n, a.N - 1);
+                k0 = min(k0, a.K - 32);
+                load_unit<BITS>(a.packed + (long)n * Kw + (k0 >> 5) * BITS, rg.w[i]);
+                const long gi = (long)n * ng + (a.g32_magic ? (int)__umulhi((uint32_t)(k0 >> 5), a.g32_magic) : (k0 >> 5));
+                rg.s[i] = a.scales[gi];
+                rg.z[i] = a.zeros[gi];
+            }
         }
     };
 
@@ -355,7 +371,9 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     auto stage_parts = [&](int kt, const Regs &rg, int buf, int i, int p0, int p1) {
         const int u = stid + NSTG * i;
         DequantConst<BITS, BF16> dq;
-        const bool ok = TRANS ? unit_row(kt, i) < a.N && unit_col(kt, i) < a.K : unit_col(kt, i) < a.K;
+        bool ok;
+        if constexpr (SYM) ok = TRANS ? unit_row(kt, i) < a.N && unit_col(kt, i) < a.K : unit_col(kt, i) < a.K;
+        else ok = rg.ok[i];
         uint32_t sr = rg.s[i], zr = rg.z[i];
         if constexpr (TIGHT) asm volatile("" : "+v"(sr), "+v"(zr));      // not kept from one part to the next
         dq.set(ok ? f16_bits_to_f32((uint16_t)sr) : 0.f, (float)zr);
