@@ -625,30 +625,49 @@ struct FinishArgs {
 
 constexpr int SIDE_PITCH = 64 + 4;       // floats of a row of u or t in LDS: read 16 bytes at a time
 
-// Sum over m of f(m, act[m * pitch]) * side[m][j0 + h], h = 0 .. 3: four adapter columns of one column of dY or x.  One
-// thread forms four gradients, so that an activation is read r / 4 times (sixteen token rows requested together) and dB is
-// written 16 bytes at a time: with one gradient per thread every activation was read r times and dB written four bytes at a
-// time (29 tokens, 4096 -> 11008, rank 32: backward pass 32.2 -> 27.8 us; rank 8: the same to 0.2 us less).  Eight gradients
-// per thread lost 0.4 us at rank 8: too few threads.
-template <bool BF16, class F>
-__device__ __forceinline__ float4_t grad4(const uint16_t *__restrict__ act, int pitch, int M, const float (*side)[SIDE_PITCH],
-                                          int j0, F f)
+// LoRA dropout: the keep bytes of one column of x, one per token row
+struct KeepColumn {
+    const uint8_t *bytes;
+    int pitch, bit;
+    float scale;
+};
+
+// v[h] += act[m * pitch] * side[m][j0 + h], h = 0 .. 3, for the token rows m0 .. m0 + ROWS, all requested before the first is used
+template <bool BF16, bool MASKED, int ROWS>
+__device__ __forceinline__ void grad_rows(const uint16_t *act, int pitch, const KeepColumn &keep, int m0,
+                                          const float (*side)[SIDE_PITCH], int j0, float4_t &v)
+{
+    uint16_t raw[ROWS];
+    uint32_t bits[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        raw[i] = act[(long)(m0 + i) * pitch];
+        if constexpr (MASKED) bits[i] = keep.bytes[(long)(m0 + i) * keep.pitch];
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        float x = cvt16<BF16>(raw[i]);
+        if constexpr (MASKED) x = (bits[i] >> keep.bit) & 1u ? x * keep.scale : 0.f;
+        const float4_t s4 = *(const float4_t *)&side[m0 + i][j0];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) v[h] += x * s4[h];
+    }
+}
+
+// Four adapter columns of one column of dY or x, summed over the tokens.  One thread forms four gradients, so that an
+// activation is read r / 4 times and dB is written 16 bytes at a time (against one gradient per thread, 4096 -> 11008, 16 to 32
+// tokens: rank 64 14 %, rank 32 10 %, rank 16 4 % and rank 8 1 % less time of the backward pass, fp16; rank 8 at 512 columns,
+// where half of the threads matters, 1 % more).  Token rows go by fours and the rest one by one: requests for sixteen rows
+// at once, clamped to the last one, took 3 to 6 % longer at ranks 8 and 16 and 6 to 15 % longer under a mask (4096 x 4096, 32
+// tokens, rank 8: 15.5 against 14.7 us, masked 18.2 against 15.9), for fewer than sixteen rows and for the code it takes.
+template <bool BF16, bool MASKED>
+__device__ __forceinline__ float4_t grad4(const uint16_t *act, int pitch, int M, const float (*side)[SIDE_PITCH], int j0,
+                                          const KeepColumn &keep)
 {
     float4_t v = {0.f, 0.f, 0.f, 0.f};
-    for (int m0 = 0; m0 < M; m0 += 16) {
-        uint16_t raw[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) raw[i] = act[(long)min(m0 + i, M - 1) * pitch];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (m0 + i < M) {
-                const float x = f(m0 + i, cvt16<BF16>(raw[i]));
-                const float4_t s4 = *(const float4_t *)&side[m0 + i][j0];
-#pragma unroll
-                for (int h = 0; h < 4; ++h) v[h] += x * s4[h];
-            }
-        }
-    }
+    int m0 = 0;
+    for (; m0 + 4 <= M; m0 += 4) grad_rows<BF16, MASKED, 4>(act, pitch, keep, m0, side, j0, v);
+    for (; m0 < M; ++m0) grad_rows<BF16, MASKED, 1>(act, pitch, keep, m0, side, j0, v);
     return v;
 }
 
@@ -716,10 +735,8 @@ __global__ __launch_bounds__(256) void gemv_bwd_finish_kernel(const FinishArgs a
         const long idx = (long)(b - a.xb) * 256 + threadIdx.x;
         if (idx >= (long)((r - a.r0) / 4) * K) return;
         const int jg = (int)(idx / K) * 4, k = (int)(idx % K);
-        const float4_t v = grad4<BF16>(a.x + k, K, M, side, a.r0 + jg, [&](int m, float xv) {
-            if constexpr (MASKED) return ((a.keep[(long)m * (K / 8) + (k >> 3)] >> (k & 7)) & 1) ? xv * a.keep_scale : 0.f;
-            else return xv;
-        });
+        const float4_t v = grad4<BF16, MASKED>(a.x + k, K, M, side, a.r0 + jg,
+                                               KeepColumn{a.keep + (k >> 3), K / 8, k & 7, a.keep_scale});
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
             float *dst = a.dA + (long)(jg + h) * K + k;
@@ -729,7 +746,7 @@ __global__ __launch_bounds__(256) void gemv_bwd_finish_kernel(const FinishArgs a
         const long idx = (long)(b - a.xb - a.ab) * 256 + threadIdx.x;
         if (idx >= (long)((r - a.r0) / 4) * N) return;
         const int jg = (int)(idx / N) * 4, n = (int)(idx % N);
-        const float4_t v = grad4<BF16>(a.dy + n, N, M, side, a.r0 + jg, [](int, float dv) { return dv; });
+        const float4_t v = grad4<BF16, false>(a.dy + n, N, M, side, a.r0 + jg, KeepColumn{});
         float4_t *dst = (float4_t *)(a.dB + (long)n * (r - a.r0) + jg);
         *dst = a.beta == 0.f ? a.sc * v : add_scaled(*dst, a.beta, a.sc, v);
     }
@@ -808,7 +825,7 @@ __global__ __launch_bounds__(256) void gemv_bwd_finish_siblings_kernel(const Fin
         const long idx = (long)((b - a.xb) % a.ab) * 256 + threadIdx.x;
         if (idx >= (long)(r / 4) * K) return;
         const int jg = (int)(idx / K) * 4, k = (int)(idx % K);
-        const float4_t v = grad4<BF16>(a.x + k, K, M, side[0], jg, [](int, float xv) { return xv; });
+        const float4_t v = grad4<BF16, false>(a.x + k, K, M, side[0], jg, KeepColumn{});
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
             float *dst = a.p[i].dA + (long)(jg + h) * K + k;
@@ -824,7 +841,7 @@ __global__ __launch_bounds__(256) void gemv_bwd_finish_siblings_kernel(const Fin
         const long idx = (long)(bb - (i ? a.p[i - 1].bb_end : 0)) * 256 + threadIdx.x;
         if (idx >= (long)(r / 4) * pr.N) return;
         const int jg = (int)(idx / pr.N) * 4, n = (int)(idx % pr.N);
-        const float4_t v = grad4<BF16>(pr.dy + n, pr.N, M, side[0], jg, [](int, float dv) { return dv; });
+        const float4_t v = grad4<BF16, false>(pr.dy + n, pr.N, M, side[0], jg, KeepColumn{});
         float4_t *dst = (float4_t *)(pr.dB + (long)n * r + jg);
         *dst = a.beta == 0.f ? a.sc * v : add_scaled(*dst, a.beta, a.sc, v);
     }
