@@ -12,38 +12,11 @@
 // 16.4 -> 13.8.  Sixteen waves instead of eight, group constants laid out without bank conflicts and a converted table of
 // them were no faster.
 #pragma once
+#include "gemv_fwd_wave_plan.hpp"
 
 namespace qlora {
 
 namespace {
-
-constexpr int FW_NW = 8;                   // waves of a workgroup; wave w takes the chunks w, w + 8, ... of its columns
-constexpr int FW_LDS = 160 * 1024;
-// columns of a chunk; half as many, so that two chunks fit, for 8-bit codes of several blocks and for 16 token rows beside 16
-// adapter rows (not for 3-bit codes: 64 columns of a row are no whole 16-byte pieces)
-constexpr int fw_ks(int bits, int nb, int ar, int xr)
-{
-    return bits != 3 && ((bits == 8 && nb > 1) || (ar == 16 && xr == 16)) ? 64 : 128;
-}
-constexpr int fw_xr(int ks, int xr) { return xr * ks < 512 ? 512 / ks : xr; }       // whole requests
-constexpr int fw_chunk(int bits, int nb, int ar, int xr)
-{
-    const int ks = fw_ks(bits, nb, ar, xr);
-    return (fw_xr(ks, xr) + ar) * 2 * ks + nb * 16 * ks * bits / 8;
-}
-constexpr int fw_tc(int ar) { return ar > 0 ? 16 : 64; }                                        // columns of t kept
-constexpr int fw_static(int ar) { return 16 * (fw_tc(ar) + 1) * 4; }
-// row pitch of the waves' partial sums: the four rows a wave writes together lie 16 banks apart
-constexpr int FW_RS = 20;
-constexpr int fw_red(int nb) { return FW_NW * (nb + 1) * 16 * FW_RS * 4; }
-
-// chunks of a wave in flight: as many as fit beside tables of up to 12 KB (6 KB if that leaves only one), four at most
-constexpr int fw_depth(int bits, int nb, int ar, int xr)
-{
-    const int chunks = FW_NW * fw_chunk(bits, nb, ar, xr), room = FW_LDS - fw_static(ar);
-    const int d = (room - 12 * 1024) / chunks;
-    return d > 4 ? 4 : (d >= 2 ? d : (room - 6 * 1024) / chunks);
-}
 
 // slot of the 16-byte piece `piece` of weight row n inside the row's PPR pieces of a chunk (its own inverse)
 template <int BITS, int PPR>
@@ -418,28 +391,12 @@ __global__ __launch_bounds__(FW_NW * 64) void gemv_fwd_wave_kernel(const FwdMult
     gemv_fwd_wave_body<BITS, BF16, NB, GR, AR, XR>(a, (int)blockIdx.x - (pi ? ma.wg_end[pi - 1] : 0));
 }
 
-inline int fw_table(int nb, int ng, int zrow) { return ((nb * 16 * ng * 2 + 1023) & ~1023) + ((nb * 16 * zrow + 1023) & ~1023) + 16; }
-
-inline int fw_wgs(const FwdMulti &m, int blocks)
+template <int BITS, bool BF16, int AR, int XR, int SHAPE>
+void launch_fwd_wave_one(FwdMulti m, hipStream_t s)
 {
-    int wgs = 0;
-    for (int i = 0; i < m.count; ++i) wgs += (blocks16(m.p[i].N) + blocks - 1) / blocks;
-    return wgs;
-}
-
-// false, and nothing launched: the stages and tables do not fit in LDS, or (one_round) the launch has more workgroups than
-// the chip has compute units
-template <int BITS, bool BF16, int NB, int GR, int AR, int XR>
-bool launch_fwd_wave_one(FwdMulti m, bool one_round, hipStream_t s)
-{
-    constexpr int D = fw_depth(BITS, NB, AR, XR);
-    if constexpr (D < 2) {
-        return false;
-    } else {
+    constexpr int NB = FW_SHAPES[SHAPE].nb, GR = FW_SHAPES[SHAPE].gr;
+    if constexpr (fw_depth(BITS, NB, AR, XR) >= 2) {            // (else the plan never names it)
         const FwdArgs &a = m.p[0];
-        const int pipe = FW_NW * D * fw_chunk(BITS, NB, AR, XR) + fw_table(NB * GR, a.ng, a.zpacked ? a.zw * 4 : a.ng);
-        const int lds = pipe > fw_red(NB * GR) ? pipe : fw_red(NB * GR);
-        if (lds > FW_LDS - fw_static(AR) || (one_round && fw_wgs(m, NB * GR) > 256)) return false;
         int wgs = 0;
         for (int i = 0; i < m.count; ++i) {
             wgs += (blocks16(m.p[i].N) + NB * GR - 1) / (NB * GR);
@@ -447,28 +404,27 @@ bool launch_fwd_wave_one(FwdMulti m, bool one_round, hipStream_t s)
         }
         auto kern = gemv_fwd_wave_kernel<BITS, BF16, NB, GR, AR, XR>;
         ensure_dynamic_lds((const void *)kern, FW_LDS - fw_static(AR));
-        QLORA_LAUNCH(kern, dim3(wgs), dim3(FW_NW * 64), lds, s, m);
-        return true;
+        QLORA_LAUNCH(kern, dim3(wgs), dim3(FW_NW * 64),
+                     fw_lds(BITS, FW_SHAPES[SHAPE], AR, XR, a.ng, a.zpacked ? a.zw * 4 : a.ng), s, m);
     }
 }
 
-// The fewest rows per workgroup with which the launch is one round of the 256 compute units (one workgroup's stages fill a
-// compute unit's LDS): the time of a round grows by 1.2 us per 16 rows from 6.5 us (K = 4096), a second round costs all of
-// it again.  Launches that need more than 128 rows per workgroup, or whose tables leave no room for that, take the most
-// rows that fit.
 template <int BITS, bool BF16, int AR, int XR>
 bool launch_fwd_wave_nb(const FwdMulti &m, hipStream_t s)
 {
-    if (launch_fwd_wave_one<BITS, BF16, 1, 1, AR, XR>(m, true, s) || launch_fwd_wave_one<BITS, BF16, 2, 1, AR, XR>(m, true, s) ||
-        launch_fwd_wave_one<BITS, BF16, 3, 1, AR, XR>(m, true, s) || launch_fwd_wave_one<BITS, BF16, 4, 1, AR, XR>(m, true, s) ||
-        launch_fwd_wave_one<BITS, BF16, 2, 2, AR, XR>(m, true, s))
-        return true;
-    for (const bool one_round : {true, false})
-        if (launch_fwd_wave_one<BITS, BF16, 3, 2, AR, XR>(m, one_round, s) ||
-            launch_fwd_wave_one<BITS, BF16, 4, 2, AR, XR>(m, one_round, s))
-            return true;
-    return launch_fwd_wave_one<BITS, BF16, 3, 1, AR, XR>(m, false, s) || launch_fwd_wave_one<BITS, BF16, 2, 1, AR, XR>(m, false, s) ||
-           launch_fwd_wave_one<BITS, BF16, 1, 1, AR, XR>(m, false, s);
+    const FwdArgs &a = m.p[0];
+    int N[MAX_SIBLINGS];
+    for (int i = 0; i < m.count; ++i) N[i] = m.p[i].N;
+    switch (fw_plan(BITS, AR, XR, a.ng, a.zpacked ? a.zw * 4 : a.ng, m.count, N)) {
+    case 0: launch_fwd_wave_one<BITS, BF16, AR, XR, 0>(m, s); return true;
+    case 1: launch_fwd_wave_one<BITS, BF16, AR, XR, 1>(m, s); return true;
+    case 2: launch_fwd_wave_one<BITS, BF16, AR, XR, 2>(m, s); return true;
+    case 3: launch_fwd_wave_one<BITS, BF16, AR, XR, 3>(m, s); return true;
+    case 4: launch_fwd_wave_one<BITS, BF16, AR, XR, 4>(m, s); return true;
+    case 5: launch_fwd_wave_one<BITS, BF16, AR, XR, 5>(m, s); return true;
+    case 6: launch_fwd_wave_one<BITS, BF16, AR, XR, 6>(m, s); return true;
+    default: return false;
+    }
 }
 
 // Serves the call if its shape allows: up to 16 token rows, K and the group size multiples of 128 (a chunk then shares its
