@@ -19,3 +19,66 @@ CASES = [(M, K, N, bits, r, dtype)
 def test_forward_blocks_per_workgroup(case):
     M, K, N, bits, r, dtype = case
     check_layer(small_inputs(M + 3 * K + N + bits, M, K, N, bits, 128, r, dtype))
+
+
+def _exact(M, K, Ns, bits, r, dtype, G=128):
+    """y (and t where it is formed in the kernel) of projections that share x, on whole-number inputs and power-of-two scales:
+    every sum is exact in fp32 whatever its order, so the result is the exact one, rounded once.  The reference is a float64
+    product on the GPU."""
+    import torch
+    from paper_2306_08162_amd import binding as ql
+
+    gen = torch.Generator(device="cuda").manual_seed(M + 3 * K + sum(Ns) + bits + r)
+    dt, flag = (torch.bfloat16, ql.QLORA_BF16) if dtype == "bf16" else (torch.float16, ql.QLORA_F16)
+
+    def ints(lo, hi, *shape, keep=1.0):
+        v = torch.randint(lo, hi + 1, shape, generator=gen, device="cuda")
+        return v if keep == 1.0 else v * (torch.rand(shape, generator=gen, device="cuda") < keep)
+
+    x = ints(-1, 1, M, K).to(dt)
+    parts = []
+    for N in Ns:
+        q, z = ints(0, 2 ** bits - 1, N, K).to(torch.uint8), ints(0, 2 ** bits - 1, N, K // G).to(torch.uint8)
+        s = torch.pow(2.0, -bits - ints(3, 4, N, K // G)).to(torch.float16)
+        A, B = ints(-1, 1, max(r, 1), K, keep=0.03).to(dt), ints(-1, 1, N, max(r, 1)).to(dt)
+        packed = torch.empty(ql.qlora_packed_words(N, K, bits), dtype=torch.int32, device="cuda")
+        ql.qlora_pack(q, packed, N, K, bits)
+        y, t = torch.zeros((M, N), dtype=dt, device="cuda"), torch.zeros((M, max(r, 1)), dtype=dt, device="cuda")
+        parts.append((q, z, s, A, B, packed, y, t))
+    ws = torch.empty(ql.qlora_siblings_workspace_bytes(list(Ns), M, K, bits, G, r), dtype=torch.uint8, device="cuda")
+    col = lambda i: [p[i] for p in parts]
+    ql.qlora_linear_fwd_siblings(x, col(5), col(2), col(1), col(3) if r else None, col(4) if r else None, col(6),
+                                 col(7) if r else None, list(Ns), M, K, bits, G, r, float(r), flag, ws)
+    for q, z, s, A, B, _, y, t in parts:
+        wd = ((q.double().view(q.shape[0], -1, G) - z.double().unsqueeze(2)) * s.double().unsqueeze(2)).view(q.shape[0], K)
+        want = x.double() @ wd.t().contiguous()
+        if r:
+            t_want = x.double() @ A.double().t().contiguous()
+            assert t_want.abs().max() <= 256                        # exact in 16 bits
+            assert torch.equal(t.double(), t_want)
+            want = want + t_want @ B.double().t().contiguous()
+        assert want.abs().max() * 2 ** (bits + 4) < 2 ** 24         # exact in fp32
+        assert torch.equal(y, want.to(torch.float32).to(dt))
+
+
+# Two groups of rows per workgroup, and more chunks of a row per wave than its ring holds: every wave waits for a chunk with the
+# whole ring in flight, refills it within the first group and on into the second one.  4352 columns are 34 chunks, which eight
+# waves share unevenly.
+RING_CASES = [(M, 4352, Ns, bits, r, dtype)
+              for Ns in [(16392,), (12296, 12280)] for bits in (2, 3, 4, 8)
+              for M, r, dtype in [(1, 8, "f16"), (4, 16, "bf16"), (5, 8, "bf16"), (16, 8, "f16"), (16, 16, "f16"), (9, 40, "bf16"),
+                                  (16, 0, "f16")]]
+
+
+@pytest.mark.parametrize("case", RING_CASES, ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(c[0], c[1], "x".join(map(str, c[2])), *c[3:]))
+def test_ring_steady_state(case):
+    _exact(*case)
+
+
+# Launches of more than one round of 256 workgroups: the shape that the plan names once the larger ones do not fit in LDS
+@pytest.mark.parametrize("case", [(16, 5120, (13824, 13832), 3, 8, "f16"), (2, 5120, (13824, 13832), 8, 8, "bf16"),
+                                  (16, 4096, (32008,), 3, 16, "f16"), (16, 5120, (13832, 13824), 4, 8, "f16"),
+                                  (16, 13824, (5128,), 3, 16, "bf16")],
+                         ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(c[0], c[1], "x".join(map(str, c[2])), *c[3:]))
+def test_several_rounds(case):
+    _exact(*case)
