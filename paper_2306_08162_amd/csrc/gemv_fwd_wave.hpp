@@ -120,16 +120,21 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
 {
     constexpr int NW = FW_NW, NT = NW * 64, R = 16 * NB, RT = R * GR;
     constexpr int KS = fw_ks(BITS, NB, AR, XMIN), SS = KS / 32, UB = KS * BITS / 32;      // MFMA steps; bytes of a lane's codes
-    constexpr int PPR = KS * BITS / 128;                                    // pieces of a weight row per chunk
+    constexpr FwShape SHAPE = {NB, GR};
+    constexpr bool PAIR = fw_pair(BITS, SHAPE, AR, XMIN);
+    constexpr int PPC = KS * BITS / 128, PPR = PAIR ? 2 * PPC : PPC;        // pieces of a weight row per chunk, per request
     constexpr int PR = KS / 8, RPI = 64 / PR;                               // pieces of an activation row; rows per request
     constexpr int XR = fw_xr(KS, XMIN);
-    constexpr int CHUNK = fw_chunk(BITS, NB, AR, XMIN), D = fw_depth(BITS, NB, AR, XMIN);
+    constexpr int D = fw_depth(BITS, SHAPE, AR, XMIN), RING = fw_ring(BITS, SHAPE, AR, XMIN);
+    constexpr int WB = R * PPR * 16, XB = (XR + AR) * 2 * KS;               // bytes of a slot: weight rows; token and adapter rows
+    constexpr int CHUNK = PAIR ? XB : WB + XB;                              // PAIR: two weight slots ahead of the others
     constexpr int WI = (R * PPR + 63) / 64, XI = XR / RPI, AI = AR / RPI;   // requests of a chunk
     constexpr int RQ = WI + XI + AI, RQ1 = WI + XI;                         // of the first group, of a later one
     constexpr int NBT = NB * GR;
-    constexpr int XOFF = R * PPR * 16, AOFF = XOFF + XR * 2 * KS;
+    constexpr int XOFF = PAIR ? 2 * WB : WB, AOFF = XOFF + XR * 2 * KS;
     constexpr int TC = fw_tc(AR);
-    static_assert(D >= 2 && (D - 1) * RQ <= 63, "two chunks in flight, countable");
+    static_assert(D >= 2 && (D - 1) * RQ <= 63 && (!PAIR || D >= 3), "two chunks in flight, countable");
+    static_assert(RING == (PAIR ? 2 * WB + D * XB : D * CHUNK), "the launch sizes LDS for this");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     __shared__ float tfull[16][TC + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -137,7 +142,7 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
     const int n0 = wg * RT, K = a.K, Kw = K * BITS / 32, r = a.r, ng = a.ng;
     const int rows_here = min(RT, a.N - n0);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
-    constexpr int TABLES = NW * D * CHUNK;
+    constexpr int TABLES = NW * RING;
     const uint16_t *sct = (const uint16_t *)(lds + TABLES);
     const uint8_t *zt = lds + TABLES + ((RT * ng * 2 + 1023) & ~1023);
     const int zrow = a.zpacked ? a.zw * 4 : ng;
@@ -179,15 +184,22 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
         const int row = RPI * j + lane / PR, piece = (lane % PR) ^ xkey(row);
         a_src[j] = (uint32_t)(((long)min(row, r - 1) * K + 8 * piece) * 2);
     }
-    const int chunks = K / KS, n_it = wave < chunks ? (chunks - wave + NW - 1) / NW : 0;
-    const uint32_t mine = lds0 + (uint32_t)wave * (D * CHUNK);
-    auto issue = [&](int g, int i, int slot) {
-        const uint32_t c = (uint32_t)(wave + NW * i), base = mine + (uint32_t)slot * CHUNK;
+    // units are dealt to the waves in turn: a chunk, or a pair of them (K % 128 == 0: pairs are whole)
+    const int units = K / (PAIR ? 2 * KS : KS), n_units = wave < units ? (units - wave + NW - 1) / NW : 0;
+    const int n_it = PAIR ? 2 * n_units : n_units;
+    auto chunk_at = [&](int i) { return PAIR ? 2 * (wave + NW * (i >> 1)) + (i & 1) : wave + NW * i; };
+    const uint32_t mine = lds0 + (uint32_t)wave * RING;
+    auto issue_w = [&](int g, int unit, uint32_t base) {
+        const uint32_t c = (uint32_t)(wave + NW * unit);
 #pragma unroll
         for (int j = 0; j < WI; ++j) {
             if ((j + 1) * 64 <= R * PPR || lane < R * PPR - 64 * j)      // a last request of fewer lanes
                 dma16(wbase, w_src[g][j] + c * (uint32_t)(PPR * 16), base + j * 1024u);
         }
+    };
+    auto issue = [&](int g, int i, int slot) {
+        const uint32_t c = (uint32_t)chunk_at(i), base = mine + (uint32_t)slot * CHUNK;
+        if constexpr (!PAIR) issue_w(g, i, base);
 #pragma unroll
         for (int j = 0; j < XI; ++j) dma16(a.x, x_src[j] + c * (uint32_t)(KS * 2), base + XOFF + j * 1024u);
         if (g == 0) {
@@ -197,6 +209,7 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) {
+        if (PAIR && (d == 0 || d == 2) && d < n_it) issue_w(0, d / 2, mine + (d / 2) * WB);
         if (d < n_it) issue(0, d, d);
         else if (GR > 1 && n_it > 0 && d < 2 * n_it) issue(1, d - n_it, d);
     }
@@ -226,10 +239,10 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
         x_at[s] = (uint32_t)(XOFF + (xr * PR + (piece ^ xkey(xr))) * 16);
         a_at[s] = (uint32_t)(AOFF + (ar * PR + (piece ^ xkey(ar))) * 16);   // adapter columns past r repeat: never used
     }
-    const uint8_t *const ring = lds + (size_t)wave * (D * CHUNK);
+    const uint8_t *const ring = lds + (size_t)wave * RING;
 
     // the tables are this wave's oldest requests: they have landed with its first chunk; the barrier publishes them
-    fw_wait_pending<GR == 1 ? RQ : RQ1>(min(D, n_it * GR) - 1);
+    fw_wait_pending<PAIR ? XI + AI : (GR == 1 ? RQ : RQ1)>(min(D, n_it * GR) - 1);
     asm volatile("s_barrier" ::: "memory");
     const bool zpk = a.zpacked != nullptr;
     const uint32_t zbits = zpk ? BITS : 8;
@@ -241,11 +254,18 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
             // chunk (g, i) has landed when at most the requests of the chunks behind it are in flight (chunks of later groups
             // bring no adapter rows: where one of them may be among those, all are counted as that short)
             constexpr int FULL = (D - 1) * (GR == 1 ? RQ : RQ1);
-            if (GR == 2 && g == 0 && i + D <= n_it) wait_vm<(D - 1) * RQ>();
+            // PAIR: behind the younger of this chunk's requests and its pair's stand those of the D - 1 chunks that follow and, if
+            // another pair follows, those of exactly one pair: pair p is requested before chunk 2 p (the first two pairs) or
+            // when pair p - 2 has been read, before chunk 2 p - 3 + D
+            if constexpr (PAIR) {
+                if (i + D <= n_it) wait_vm<(D - 1) * (XI + AI) + WI>();
+                else fw_wait_pending<XI + AI>(n_it - 1 - i);
+            } else if (GR == 2 && g == 0 && i + D <= n_it) wait_vm<(D - 1) * RQ>();
             else if (i + D <= n_it * (GR - g)) wait_vm<FULL>();
             else fw_wait_pending<GR == 1 ? RQ : RQ1>(n_it * (GR - g) - 1 - i);
-            const uint8_t *buf = ring + slot * CHUNK;
-            const int grp = group_of((wave + NW * i) * KS, a.magic);
+            const uint8_t *buf = ring + slot * CHUNK, *wbuf = PAIR ? ring + ((i >> 1) & 1) * WB : buf;
+            const int first = PAIR ? (i & 1) * PPC : 0;      // the chunk's first piece in a weight row
+            const int grp = group_of(chunk_at(i) * KS, a.magic);
             const uint32_t zoff = zpk ? (uint32_t)(grp * BITS) >> 3 : (uint32_t)grp, zshift = zpk ? (grp * BITS) & 7 : 0;
             const uint32_t s_at = (uint32_t)li * s_row + (uint32_t)grp * 2u, z_at = (uint32_t)li * z_row + zoff;
             u16x8_t xf[SS], af[SS], xo[SS];
@@ -260,7 +280,7 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const int n = nb * 16 + li;
-                const uint8_t *rowp = buf + n * (PPR * 16);
+                const uint8_t *rowp = wbuf + n * (PPR * 16);
                 if constexpr (BITS == 3) {
                     const uint32_t *p = (const uint32_t *)(rowp + 12 * q);
 #pragma unroll
@@ -268,12 +288,12 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
                 } else if constexpr (UB == 32) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        const u32x4_t v = *(const u32x4_t *)(rowp + fw_slot<BITS, PPR>(n, 2 * q + h) * 16);
+                        const u32x4_t v = *(const u32x4_t *)(rowp + fw_slot<BITS, PPR>(n, first + 2 * q + h) * 16);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) w[nb][(4 * h + e) % BITS] = v[e];
                     }
                 } else if constexpr (UB == 16) {
-                    const u32x4_t v = *(const u32x4_t *)(rowp + fw_slot<BITS, PPR>(n, q) * 16);
+                    const u32x4_t v = *(const u32x4_t *)(rowp + fw_slot<BITS, PPR>(n, first + q) * 16);
 #pragma unroll
                     for (int h = 0; h < 4; ++h) w[nb][h] = v[h];
 #pragma unroll
@@ -297,6 +317,7 @@ __device__ __forceinline__ void gemv_fwd_wave_body(const FwdArgs &a, const int w
                 zp[nb] = __builtin_amdgcn_ubfe(z, (uint32_t)zshift, zbits);
             }
             wait_lds();                                      // the chunk is in registers: its slot may be refilled
+            if (PAIR && (i & 1) && i + 3 < n_it) issue_w(0, (i >> 1) + 2, mine + ((i >> 1) & 1) * WB);
             if (i + D < n_it) issue(g, i + D, slot);
             else if (g + 1 < GR && i + D - n_it < n_it) issue(g + 1, i + D - n_it, slot);
             slot = slot + 1 == D ? 0 : slot + 1;
@@ -398,7 +419,7 @@ template <int BITS, bool BF16, int AR, int XR, int SHAPE>
 void launch_fwd_wave_one(FwdMulti m, hipStream_t s)
 {
     constexpr int NB = FW_SHAPES[SHAPE].nb, GR = FW_SHAPES[SHAPE].gr;
-    if constexpr (fw_depth(BITS, NB, AR, XR) >= 2) {            // (else the plan never names it)
+    if constexpr (fw_depth(BITS, FW_SHAPES[SHAPE], AR, XR) >= 2) {            // (else the plan never names it)
         const FwdArgs &a = m.p[0];
         int wgs = 0;
         for (int i = 0; i < m.count; ++i) {

@@ -84,6 +84,7 @@ def test_cheapest_shape_that_fits(plan):
     (4, 8, 4, 4096, [11008, 11008], 96),        # one round
     (2, 8, 16, 4096, [4096, 4096, 4096], 64),
     (2, 16, 16, 13824, [5120], 32),
+    (8, 8, 16, 13824, [5120], 32),
 ])
 def test_rows_of_a_workgroup(plan, bits, ar, xr, K, Ns, rows):
     (pick, shapes), = plan([(bits, ar, xr, K // 128, K // 128, Ns)])[0]
@@ -93,3 +94,9 @@ def test_rows_of_a_workgroup(plan, bits, ar, xr, K, Ns, rows):
 def test_one_block_of_many_rounds_is_left_to_the_older_kernel(plan):
     (pick, _), = plan([(3, 16, 16, 13824 // 128, 13824 // 128, [5120])])[0]
     assert pick == -1
+
+
+def test_8_bit_rows_come_in_whole_lines(plan):
+    """Without an adapter the 64-row shape with 128-column chunks (2 x 2 blocks) stands in for that of four blocks."""
+    (pick, shapes), = plan([(8, 0, 16, 5120 // 128, 5120 // 128, [13824])])[0]
+    assert shapes[pick][:2] == (2, 2)

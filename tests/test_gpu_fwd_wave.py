@@ -82,3 +82,16 @@ def test_ring_steady_state(case):
                          ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(c[0], c[1], "x".join(map(str, c[2])), *c[3:]))
 def test_several_rounds(case):
     _exact(*case)
+
+
+# 8-bit codes in 64-column chunks of one group: weight rows arrive for two chunks at once.  1 to 34 chunk pairs of a row, so that
+# waves have none, one, two and more of them; one block of rows beside 16 adapter rows and two beside 8; token rows of one
+# request and of two.  (Without an adapter two blocks fit with 128-column chunks.)
+PAIR_CASES = [(M, K, (N,), 8, r, dtype)
+              for K in (128, 256, 1024, 1152, 2176, 3200, 4352) for N, r in [(4112, 8), (8192, 8), (8192, 0), (264, 16)]
+              for M, dtype in [(16, "f16"), (5, "bf16"), (2, "f16")] if N * (K // 128) % 16 == 0]
+
+
+@pytest.mark.parametrize("case", PAIR_CASES, ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(c[0], c[1], c[2][0], *c[3:]))
+def test_paired_weight_requests(case):
+    _exact(*case)
