@@ -11,7 +11,8 @@
 // same fp16 values 1024 + c * 2^p (fp32 holds their products with a scale exactly: 11 bits each) go through one
 // mixed-precision fma per code, (1024 + c * 2^p) * (s * 2^-p) - (1024 * 2^-p + z) * s = s (c - z) exactly, and are packed
 // with the hardware bf16 conversion: 2.0 to 3.0 instructions per code where extracting and converting every code by
-// itself took 2.5 to 3.4.
+// itself took 2.5 to 3.4.  8-bit codes keep that form: v_cvt_f32_ubyte takes any byte of a word, and the mixed-precision
+// form was 1 to 7 % slower where the pass has little else to do (17 tokens, 13824 -> 5120, no adapter: 36.6 against 34.1 us).
 #pragma once
 #include "common.hpp"
 
@@ -44,14 +45,14 @@ template <int BITS>
 struct DequantConst<BITS, true> {
     // codes sit at bit p = STEP i of a 16-bit lane, i < NP
     static constexpr int NP = BITS == 2 ? 4 : (BITS == 8 ? 1 : 2), STEP = BITS;
-    float mul[NP], off[NP];     // s * 2^-p and -(1024 * 2^-p + z) * s
+    float mul[NP], off[NP];     // s * 2^-p and -(1024 * 2^-p + z) * s (8-bit codes: s and -z * s)
     __device__ __forceinline__ void set(float sc, float z)
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const float inv = 1.f / (float)(1 << (STEP * i));
             mul[i] = sc * inv;
-            off[i] = -(1024.f * inv + z) * sc;
+            off[i] = BITS == 8 ? -z * sc : -(1024.f * inv + z) * sc;
         }
     }
 };
@@ -122,11 +123,11 @@ __device__ __forceinline__ u16x8_t dequant8(const uint32_t (&w)[BITS], int part,
                 out[i] = fp16_pair<SCALE>(spread_byte(x >> (6 * i), 0) & (0x00380007u | MAGIC), mul, c.off[0], c.s2);
         }
     } else {
+        typedef float float2_t __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
         constexpr uint32_t MAGIC = 0x64006400u;
         // two neighbouring codes as (1024 + c * 2^p, 1024 + c' * 2^p'), p and p' given by their index into c.mul
         auto pair = [&](uint32_t bits, int p0, int p1) {
-            typedef float float2_t __attribute__((ext_vector_type(2)));
-            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
             const half2_t h = __builtin_bit_cast(half2_t, bits);
             const float2_t f = {__builtin_fmaf((float)h[0], c.mul[p0], c.off[p0]),
                                 __builtin_fmaf((float)h[1], c.mul[p1], c.off[p1])};
@@ -144,8 +145,12 @@ __device__ __forceinline__ u16x8_t dequant8(const uint32_t (&w)[BITS], int part,
             }
         } else if constexpr (BITS == 8) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                out[i] = pair(__builtin_amdgcn_perm(MAGIC, w[2 * part + (i >> 1)], (i & 1) ? 0x05030502u : 0x05010500u), 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t b = w[2 * part + (i >> 1)] >> (16 * (i & 1));
+                const float2_t f = {__builtin_fmaf((float)(b & 0xffu), c.mul[0], c.off[0]),
+                                    __builtin_fmaf((float)((b >> 8) & 0xffu), c.mul[0], c.off[0])};
+                out[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+            }
         } else {
             const uint32_t x = window<BITS>(w, 24 * part);
 #pragma unroll
