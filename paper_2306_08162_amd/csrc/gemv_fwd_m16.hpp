@@ -5,11 +5,12 @@
 // through, not the bytes: a lane that fetches its own MFMA fragment of a 2-bit weight touches 8 bytes of a row, so a
 // wave instruction brings in sixteen 32-byte pieces, and the group constants cost two more such instructions per
 // fragment.  Here nothing is fetched fragment-wise.  A workgroup of eight waves owns 16 NB weight rows and walks K in
-// stages of 8 KS columns (KS = 64): per stage the
-// packed words of all its rows (row segments of KS BITS bytes, whole cache lines), the token rows of x (16 or 32; only
-// the requests that hold rows below M are made) and the adapter rows of A arrive by direct-to-LDS loads of 1 KB per
-// instruction, two stages in flight, and every wave takes the fragments of its KS contraction indices from LDS.  The
-// group constants of all the workgroup's rows are copied to LDS once, at the start.
+// stages of 8 KS columns (KS = 64): per stage the packed words of all its rows (row segments of KS BITS bytes, whole cache
+// lines), the token rows of x (16 or 32; only the requests that hold rows below M are made) and the adapter rows of A
+// arrive by direct-to-LDS loads of 1 KB per instruction, two stages in flight, and every wave takes the fragments of its
+// KS contraction indices from LDS.  The group constants of all the workgroup's rows are copied to LDS once, at the
+// start.  Up to 16 token rows beside at most 16 adapter rows the kernel of gemv_fwd_wave.hpp is faster; 3-bit codes have
+// 12-byte units, which 64-column slices would cut.
 //
 // Layout of a stage in LDS: per wave a slice of x (16 MB rows x KS columns) and an AR-row slice of A (piece c of row
 // w in slot (KS / 8) w + (c ^ w mod KS / 8), as in the staged kernel); then the weight chunk, row n at n * KS BITS
@@ -22,22 +23,20 @@ namespace {
 
 constexpr int M16_NW = 8;                  // waves of a workgroup; wave w owns columns KS w .. KS w + KS of a stage
 constexpr int M16_LDS = 160 * 1024;
-// Columns of a wave per stage and stages in LDS: 64 columns, so that 32 rows of x or of A per wave fit, and two stages.
-constexpr int m16_ks(int, int, int) { return 64; }
-constexpr int m16_nst(int, int, int) { return 2; }
+constexpr int M16_KS = 64;                 // so that 32 rows of x or of A per wave fit twice
+constexpr int M16_NST = 2;                 // stages in LDS
 
 // slot of the 16-byte piece `piece` of weight row n inside the row's stage segment of PPR pieces (its own inverse)
-template <int BITS, int PPR>
+template <int PPR>
 __device__ __forceinline__ int wswz(int n, int piece)
 {
-    if constexpr (BITS == 3) return 3 * ((piece / 3) ^ (n & 7)) + piece % 3;       // whole units of 12 bytes stay together
-    else return piece ^ (n & (PPR < 16 ? PPR - 1 : 15));
+    return piece ^ (n & (PPR < 16 ? PPR - 1 : 15));
 }
 
-constexpr int m16_xa(int bits, int ar, int mb) { return (16 * mb + ar) * 2 * m16_ks(bits, mb, ar); }   // a wave's slices of x and A
+constexpr int m16_xa(int ar, int mb) { return (16 * mb + ar) * 2 * M16_KS; }   // a wave's slices of x and A
 constexpr int m16_stage(int bits, int nb, int ar, int mb)
 {
-    return M16_NW * m16_xa(bits, ar, mb) + nb * 16 * m16_ks(bits, mb, ar) * bits;
+    return M16_NW * m16_xa(ar, mb) + nb * 16 * M16_KS * bits;
 }
 constexpr int m16_table(int nb, int ng, int zrow)     // scales (2 B per group), zero-points (zrow bytes per row: one per
 {                                                     // group, or the row's packed words), each filled in whole KB
@@ -64,12 +63,13 @@ __device__ __forceinline__ void wait_vm_upto(int n)
 template <int BITS, bool BF16, int NB, int AR, int MB>
 __device__ __forceinline__ void gemv_fwd_m16_body(const FwdArgs &a, const int wg)
 {
+    static_assert(BITS != 3 && (MB == 2 || AR == 32), "what launch_fwd_m16 launches");
     constexpr int NW = M16_NW, NT = NW * 64, R = 16 * NB, XROWS = 16 * MB;
-    constexpr int KS = m16_ks(BITS, MB, AR), KC = NW * KS, NST = m16_nst(BITS, MB, AR), SS = KS / 32;   // SS: MFMA steps of a wave per stage
+    constexpr int KS = M16_KS, KC = NW * KS, NST = M16_NST, SS = KS / 32;   // SS: MFMA steps of a wave per stage
     constexpr int PPR = KS * BITS / 16, UB = KS * BITS / 32; // pieces of a weight row per stage; bytes of a lane's codes
     constexpr int PR = KS / 8, RPI = 64 / PR;                // pieces of an activation row per stage; rows per request
     constexpr int XBYTES = 2 * XROWS * KS;                   // a wave's slice of x
-    constexpr int XA = m16_xa(BITS, AR, MB), WOFF = NW * XA, STAGE = m16_stage(BITS, NB, AR, MB);
+    constexpr int XA = m16_xa(AR, MB), WOFF = NW * XA, STAGE = m16_stage(BITS, NB, AR, MB);
     constexpr int WI = R * PPR / 64;                         // weight requests per stage, dealt out wave by wave
     constexpr int WI_HI = (WI + NW - 1) / NW, WI_LO = WI / NW;
     constexpr int XIX = XROWS / RPI, XIA = AR / RPI, XI = XIX + XIA;   // requests of a wave's own slices
@@ -94,7 +94,7 @@ __device__ __forceinline__ void gemv_fwd_m16_body(const FwdArgs &a, const int wg
     for (int c = 0; c < WI_HI; ++c) {
         const int e = 64 * (wave + NW * c) + lane, n = min(e / PPR, R - 1), slot = e % PPR;
         w_src[c] = (uint32_t)min(n, rows_here - 1) * row_bytes;
-        w_piece[c] = (uint32_t)wswz<BITS, PPR>(n, slot) * 16u;
+        w_piece[c] = (uint32_t)wswz<PPR>(n, slot) * 16u;
     }
     // requests that bring in token rows below M (a request moves RPI rows); the rows of x past them are never fetched:
     // what the MFMAs make of the stale LDS there lands in output rows that are not stored
@@ -209,36 +209,30 @@ __device__ __forceinline__ void gemv_fwd_m16_body(const FwdArgs &a, const int wg
         for (int nb = 0; nb < NB; ++nb) {
             const int n = nb * 16 + li;
             const uint8_t *rowp = wc + n * (PPR * 16);
-            if constexpr (BITS == 3) {
-                const uint32_t *p = (const uint32_t *)(rowp + (wave ^ (n & 7)) * 48 + 12 * q);
+            const int ob = (4 * wave + q) * UB;           // the lane's codes inside the row's segment
+            if constexpr (UB >= 16) {
 #pragma unroll
-                for (int i = 0; i < 3; ++i) w[nb][i] = p[i];
-            } else {
-                const int ob = (4 * wave + q) * UB;           // the lane's codes inside the row's segment
-                if constexpr (UB >= 16) {
+                for (int h = 0; h < UB / 16; ++h) {
+                    const u32x4_t v = *(const u32x4_t *)(rowp + wswz<PPR>(n, (ob >> 4) + h) * 16);
 #pragma unroll
-                    for (int h = 0; h < UB / 16; ++h) {
-                        const u32x4_t v = *(const u32x4_t *)(rowp + wswz<BITS, PPR>(n, (ob >> 4) + h) * 16);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) w[nb][4 * h + i] = v[i];
-                    }
-                } else if constexpr (UB == 8) {
-                    const u32x2_t v = *(const u32x2_t *)(rowp + wswz<BITS, PPR>(n, ob >> 4) * 16 + (ob & 15));
-                    w[nb][0] = v[0];
-                    w[nb][1] = v[1];
-                } else {
-                    w[nb][0] = *(const uint32_t *)(rowp + wswz<BITS, PPR>(n, ob >> 4) * 16 + (ob & 15));
+                    for (int i = 0; i < 4; ++i) w[nb][4 * h + i] = v[i];
                 }
-#pragma unroll
-                for (int i = UB / 4; i < BITS; ++i) w[nb][i] = 0u;
+            } else if constexpr (UB == 8) {
+                const u32x2_t v = *(const u32x2_t *)(rowp + wswz<PPR>(n, ob >> 4) * 16 + (ob & 15));
+                w[nb][0] = v[0];
+                w[nb][1] = v[1];
+            } else {
+                w[nb][0] = *(const uint32_t *)(rowp + wswz<PPR>(n, ob >> 4) * 16 + (ob & 15));
             }
+#pragma unroll
+            for (int i = UB / 4; i < BITS; ++i) w[nb][i] = 0u;
             sc[nb] = live ? f16_bits_to_f32(sct[n * ng + grp]) : 0.f;
             zp[nb] = a.zpacked ? (float)packed_zero<BITS>((const uint32_t *)(zt + n * zrow), grp) : (float)zt[n * ng + grp];
         }
         wait_lds();                                          // everything of this stage is in registers
         const bool more = st + 2 < S;                        // workgroup-uniform
-        const int fill = (st + 2) % NST;                     // two stages: the buffer just read, once every wave is done
-        if (NST == 2 && more) __syncthreads();               // with it; three: the one every wave left a step ago
+        const int fill = bi;                                 // the buffer just read, once every wave is done with it
+        if (more) __syncthreads();
         if (!live) {
             if (more) issue(st + 2, fill);
             continue;
@@ -356,7 +350,7 @@ template <int BITS>
 inline int m16_nb_max(int ar, int ng, int zrow, int mb)
 {
     for (int nb = 4; nb >= 1; --nb)
-        if (m16_nst(BITS, mb, ar) * m16_stage(BITS, nb, ar, mb) + m16_table(nb, ng, zrow) + m16_static(ar, mb) <= M16_LDS)
+        if (M16_NST * m16_stage(BITS, nb, ar, mb) + m16_table(nb, ng, zrow) + m16_static(ar, mb) <= M16_LDS)
             return nb;
     return 0;
 }
@@ -364,7 +358,7 @@ inline int m16_nb_max(int ar, int ng, int zrow, int mb)
 template <int BITS, bool BF16, int NB, int AR, int MB>
 void launch_fwd_m16_one(FwdMulti m, hipStream_t s)
 {
-    const int pipe = m16_nst(BITS, MB, AR) * m16_stage(BITS, NB, AR, MB) + m16_table(NB, m.p[0].ng, m16_zrow(m.p[0]));
+    const int pipe = M16_NST * m16_stage(BITS, NB, AR, MB) + m16_table(NB, m.p[0].ng, m16_zrow(m.p[0]));
     const int lds = pipe > m16_red(NB, MB, AR) ? pipe : m16_red(NB, MB, AR);
     int wgs = 0;
     for (int i = 0; i < m.count; ++i) {
@@ -379,19 +373,18 @@ void launch_fwd_m16_one(FwdMulti m, hipStream_t s)
 template <int BITS, bool BF16, int AR, int MB>
 void launch_fwd_m16_nb(const FwdMulti &m, int nb, hipStream_t s)
 {
-    constexpr int NST = m16_nst(BITS, MB, AR);
     switch (nb) {
     case 4:
-        if constexpr (NST * m16_stage(BITS, 4, AR, MB) < M16_LDS) { launch_fwd_m16_one<BITS, BF16, 4, AR, MB>(m, s); return; }
+        if constexpr (M16_NST * m16_stage(BITS, 4, AR, MB) < M16_LDS) { launch_fwd_m16_one<BITS, BF16, 4, AR, MB>(m, s); return; }
         [[fallthrough]];
     case 3:
-        if constexpr (NST * m16_stage(BITS, 3, AR, MB) < M16_LDS) { launch_fwd_m16_one<BITS, BF16, 3, AR, MB>(m, s); return; }
+        if constexpr (M16_NST * m16_stage(BITS, 3, AR, MB) < M16_LDS) { launch_fwd_m16_one<BITS, BF16, 3, AR, MB>(m, s); return; }
         [[fallthrough]];
     case 2:
-        if constexpr (NST * m16_stage(BITS, 2, AR, MB) < M16_LDS) { launch_fwd_m16_one<BITS, BF16, 2, AR, MB>(m, s); return; }
+        if constexpr (M16_NST * m16_stage(BITS, 2, AR, MB) < M16_LDS) { launch_fwd_m16_one<BITS, BF16, 2, AR, MB>(m, s); return; }
         [[fallthrough]];
     default:
-        if constexpr (NST * m16_stage(BITS, 1, AR, MB) < M16_LDS) launch_fwd_m16_one<BITS, BF16, 1, AR, MB>(m, s);
+        if constexpr (M16_NST * m16_stage(BITS, 1, AR, MB) < M16_LDS) launch_fwd_m16_one<BITS, BF16, 1, AR, MB>(m, s);
     }
 }
 
