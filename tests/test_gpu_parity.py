@@ -439,6 +439,27 @@ def test_large_tile_kernel(case):
     check_layer(inp)
 
 
+# bf16 at the other code widths, whose staging differs (loads per stage, and with them the waits; dequantisation): five stages and a
+# ragged tile row backward, a contraction that ends inside a stage, five stages forward, and both passes exactly
+LARGE_TILE_BF16_CASES = [c for bits in (3, 4, 8)
+                         for c in [(4104, 4096, 320, bits, 64, 16, "bf16"), (4096, 4096, 104, bits, 64, 8, "bf16"),
+                                   (4096, 320, 4096, bits, 64, 8, "bf16")]]
+
+
+@pytest.mark.parametrize("case", LARGE_TILE_BF16_CASES, ids=lambda c: "M{}_K{}_N{}_b{}_G{}_r{}_{}".format(*c))
+def test_large_tile_kernel_bf16(case):
+    M, K, N, bits, G, r, dtype = case
+    check_layer(small_inputs(M + 3 * K + 7 * N + bits, M, K, N, bits, G, r, dtype))
+
+
+@pytest.mark.parametrize("case", [(4096, 4096, 320, bits, 64, 8, "bf16") for bits in (3, 4, 8)]
+                         + [(4096, 320, 4096, bits, 64, 8, "bf16") for bits in (3, 4, 8)],
+                         ids=lambda c: "M{}_K{}_N{}_b{}_G{}_r{}_{}".format(*c))
+def test_large_tile_kernel_bf16_exact(case):
+    M, K, N, bits, G, r, dtype = case
+    check_layer(integer_inputs(M + K + N + bits, M, K, N, bits, G, r, dtype, density=0.03), exact=True)
+
+
 @pytest.mark.parametrize("case", [(4096, 256, 4096, 4, 128, 8, "f16"), (4096, 4096, 256, 2, 128, 8, "bf16"),
                                   (4104, 4096, 320, 8, 64, 8, "f16")],
                          ids=lambda c: "M{}_K{}_N{}_b{}_G{}_r{}_{}".format(*c))
