@@ -474,7 +474,7 @@ def run_mfma_probe(iters: int = 40000, reps: int = 4):
             e1.synchronize()
             tf = iters * ql.MFMA_PROBE_FLOP_PER_ITER / (e0.elapsed_ms(e1) * 1e-3) / 1e12
         res[name + "_TFLOPs"] = round(tf, 1)
-    res["what"] = "register-resident v_mfma_f32_32x32x16_f16 only, 2 waves per SIMD, ~10 ms launches"
+    res["what"] = "register-resident v_mfma_f32_16x16x32_f16 only, in the GEMM's order, 2 waves per SIMD, ~10 ms launches"
     return res
 
 

@@ -42,10 +42,11 @@ int qlora_profile_gemm_span(int span);
 int qlora_stream_probe(const void *src, unsigned long long bytes, unsigned int *out, void *stream);
 
 /*
- * Runs `iters` rounds of eight register-resident v_mfma_f32_32x32x16_f16 per wave on 256 workgroups of eight waves
+ * Runs `iters` rounds of sixteen register-resident v_mfma_f32_16x16x32_f16 per wave on 256 workgroups of eight waves
  * (two per SIMD: the matrix pipe is never idle) and nothing else: no memory, no LDS, no other arithmetic.  Its rate,
- * 256 x 8 x iters x 8 x 32768 flop over its duration, is what the matrix cores of this machine sustain.  random != 0:
- * the operands are pseudo-random fp16 values in (-1, 1) and change from one MFMA to the next (four register sets);
+ * 256 x 8 x iters x 16 x 16384 flop over its duration, is what the matrix cores of this machine sustain.  random != 0:
+ * the operands are pseudo-random fp16 values in (-1, 1), four register sets of each, multiplied all with all in the order
+ * of the GEMM (a serpentine: one operand changes from one MFMA to the next);
  * random == 0: small constants, the same for every MFMA.  The two differ because the chip's clock follows its power
  * draw, and that follows the data.  out: device pointer to 256 * 512 floats (one per thread, so that nothing is
  * optimised away), 16-byte aligned.  iters >= 1.  Returns 0, or the QLORA_E_* codes of qlora.h for a NULL pointer

@@ -28,7 +28,7 @@ EXPORTS = ["qlora_status_string", "qlora_packed_words", "qlora_workspace_bytes",
 BENCH_EXPORTS = ["qlora_profile_gemm", "qlora_profile_gemm_span", "qlora_stream_probe", "qlora_mfma_probe"]        # include/qlora_bench.h
 STREAM_PROBE_WORDS = 1024
 MFMA_PROBE_FLOATS = 256 * 512              # floats of the probe's output
-MFMA_PROBE_FLOP_PER_ITER = 256 * 8 * 8 * 32768   # per round: workgroups x waves x MFMAs x flop of a 32x32x16 MFMA
+MFMA_PROBE_FLOP_PER_ITER = 256 * 8 * 16 * 16384  # per round: workgroups x waves x MFMAs x flop of a 16x16x32 MFMA
 MAX_SIBLINGS, SIBLINGS_MAX_M = 4, 16
 
 _lib = None

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     // step's MFMAs: 5 to 23 registers spilled otherwise (4096 x 4096 x 4096, INT2: 167 us against 140)
     constexpr bool TIGHT = SYM && BF16 && TRANS;
     constexpr int XDMA = BM / 8 / MW;               // direct-to-LDS loads per MFMA wave per stage (8 rows each)
-    static_assert(XDMA >= 4 && XDMA % 4 == 0, "loads are spread over the four k-steps");
+    static_assert(XDMA >= 4 && XDMA % 4 == 0, "loads are spread over the steps of a stage");
     constexpr int WU = 2 * BN / NSTG;               // 32-code weight units per staging thread per stage
     constexpr int XS = BM * BK;                     // halfs per activation stage (128-byte rows, swizzled)
     constexpr int NXS = GEMM_NXS;                   // (2 would let two workgroups share a CU's LDS: measured slower)
@@ -396,10 +396,10 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
 
     if constexpr (SYM) {
         // ---- symmetric waves: every wave requests an MW-th of the activation tile, stages an MW-th of the weight
-        //      stage and multiplies its own block.  Per 64-deep stage and wave: four k-steps of MI NI MFMAs, XDMA
-        //      direct-to-LDS requests (a quarter per k-step), WU units dequantised into the other weight buffer (a
-        //      quarter of them per k-step) and WU units requested from memory NSETS stages ahead.
-        static_assert((WU == 1 || WU == 2) && NXS == 3, "a quarter of the staging per k-step; three activation stages");
+        //      stage and multiplies its own block.  Per 64-deep stage and wave: eight steps of MH NI MFMAs, every other one
+        //      with a quarter of the unit that is dequantised into the other weight buffer, the ones between with one of
+        //      the XDMA direct-to-LDS requests; and one unit requested from memory NSETS stages ahead.
+        static_assert(NXS == 3, "three activation stages");
         const int drow = lane >> 3;
         const int dchunk = ((lane & 7) ^ ((4 * cw + (drow >> 1)) & 7)) * 8;
         const uint32_t xs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t *)xs;
@@ -776,6 +776,10 @@ void launch_tiles(GemmArgs &a, hipStream_t s)
     // contraction split over several workgroups per tile.  A round of 128-row tiles takes 0.6 times as long as one of
     // 256-row tiles (4096 x 4096, INT4, fp16: 39 and 64 us forward, 42 and 66 backward), so two rounds of them lose to one:
     // M = 1397, 4096 x 4096, bf16 INT4 (352 tiles of 128 rows or 192 of 256) 79 -> 52 us forward, 76 -> 56 backward.
+    // Larger launches take 256-row tiles whatever the last round holds.  That is dear where it holds a few: 513 to 640 tokens
+    // to 11008 columns are 258 of them, and the backward pass takes 130 us where two rounds of 128-row tiles would take 92;
+    // but the ratio alone decides no better, for full rounds differ from it (3000 tokens, 4096 x 11008: 1.14 times as long
+    // by 0.6 * rounds).
     if constexpr (BM == 256) {
         if (((a.M + 127) / 128) * a.tiles_n <= 256) {
             a.tiles_m = (a.M + 127) / 128;

@@ -4,9 +4,10 @@
 // (gemv_bwd.hip).
 //
 //   forward  (M <= 32)  y = x Wd^T + sc * t B^T with t = x A^T computed by the same v_mfma_f32_16x16x32 (one extra
-//            fragment of A per k-step); a workgroup owns up to four blocks of 16 weight rows, its waves split K.
-//            The packed words, x and A are staged through LDS by direct-to-LDS loads (gemv_fwd_m16.hpp); shapes
-//            that kernel does not take stage x and A only and fetch packed words fragment-wise (gemv_fwd_impl.hpp).
+//            fragment of A per k-step); a workgroup owns up to eight blocks of 16 weight rows, its waves split K.
+//            The packed words, x and A are staged through LDS by direct-to-LDS loads: up to 16 token rows beside at most 16
+//            adapter rows by every wave for itself (gemv_fwd_wave.hpp), else by the workgroup (gemv_fwd_m16.hpp); shapes
+//            that neither takes stage x and A only and fetch packed words fragment-wise (gemv_fwd_impl.hpp).
 //
 // This file holds the host side of the forward pass; the kernels are instantiated per code width in
 // gemv_fwd_b{2,3,4,8}.hip.

@@ -327,7 +327,7 @@ namespace {
 template <int BITS, bool BF16>
 bool launch_fwd_mb(const FwdMulti &m, int rg, hipStream_t s)
 {
-    const bool zpacked = m.p[0].zpacked != nullptr;       // only the kernel with staged group constants reads those
+    const bool zpacked = m.p[0].zpacked != nullptr;       // the first two kernels read those
     if (launch_fwd_wave<BITS, BF16>(m, rg, s)) return true;
     if (launch_fwd_m16<BITS, BF16>(m, rg, s)) return true;
     if (zpacked) return false;

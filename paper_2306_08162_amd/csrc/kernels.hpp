@@ -44,7 +44,7 @@ void launch_pack_permuted(const uint8_t *codes, const int32_t *perm, uint32_t *p
 void launch_gather_columns(const void *src, const int32_t *index, void *dst, int M, int K, hipStream_t s);
 // benchmark instrumentation: 1024 partial exclusive-ors of the 32-bit words of a buffer, read once with 16-byte loads
 void launch_stream_probe(const void *src, size_t bytes, uint32_t *out, hipStream_t s);
-// benchmark instrumentation: iters x 8 register-resident 32x32x16 fp16 MFMAs per wave, 256 workgroups of 8 waves
+// benchmark instrumentation: iters x 16 register-resident 16x16x32 fp16 MFMAs per wave, 256 workgroups of 8 waves
 void launch_mfma_probe(float *out, int iters, bool random, hipStream_t s);
 
 // adapters.hip -- the rank-r side products and the adapter gradients
@@ -105,8 +105,8 @@ constexpr int MAX_SIBLINGS = 4;                // projections that read the same
 // y[i] (and t_out[i], if not NULL and the kernel forms t) from one launch up to 16 token rows, one launch each above;
 // t_in[i] is used when the kernel does not form t (ranks above 32, or t_given: t was computed beforehand, e.g. under
 // dropout).  The arrays are host arrays of `count` device pointers.  With `zpacked` (the zero-points of each
-// projection in their bit-packed storage form, [N, zero_words]) `zeros` is not read; only the staged kernel for up
-// to 16 rows reads that form, and where it does not take the shape nothing is launched and false comes back.
+// projection in their bit-packed storage form, [N, zero_words]) `zeros` is not read; the kernels of gemv_fwd_wave.hpp and
+// gemv_fwd_m16.hpp read that form, and where neither takes the shape nothing is launched and false comes back.
 bool launch_fwd_small(const Problem &p, int count, const void *x, const uint32_t *const *packed,
                       const void *const *scales, const uint8_t *const *zeros, const void *const *A,
                       const void *const *B, const void *const *t_in, void *const *t_out, void *const *y, const int *N,

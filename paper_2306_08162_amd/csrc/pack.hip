@@ -326,11 +326,11 @@ __device__ __forceinline__ uint32_t probe_mix(uint32_t x)
 template <bool RANDOM>
 __global__ __launch_bounds__(MFMA_PROBE_THREADS) void mfma_probe_kernel(float *__restrict__ out, int iters)
 {
-    float16_t acc[8];
+    float4_t acc[4][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+        for (int j = 0; j < 4; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
     half8_t a[4], b[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -347,14 +347,20 @@ __global__ __launch_bounds__(MFMA_PROBE_THREADS) void mfma_probe_kernel(float *_
         }
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i & 3], b[(i + (i >> 2)) & 3], acc[i], 0, 0, 0);
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int j = (i & 1) ? 3 - jj : jj;              // each shares one operand with the one before, as in the GEMM
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
     }
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sum += acc[i][v];
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sum += acc[i][j][v];
     out[blockIdx.x * MFMA_PROBE_THREADS + threadIdx.x] = sum;
 }
 
