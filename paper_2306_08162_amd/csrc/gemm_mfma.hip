@@ -12,12 +12,12 @@
 // The dequantised weight never reaches HBM.  The rank-r LoRA term is folded in as extra contraction steps.
 //
 // What bounds the large launches is power: the matrix pipe's clock falls with the operand bits that change.  A
-// register-resident loop on random fp16 operands sustains 1590 TFLOP/s with 32x32x16 MFMAs and 1870 with 16x16x32 (half
-// the accumulator traffic per flop; bf16 1770 and 2015).  The 16x16x32 form, weights as the first operand and the MFMAs
-// of a step in serpentine order take the fp16 step at 2048 x 4096 x 4096, INT4, from 153 to 144 us, 4096 x 11008 -> 4096,
-// INT3, from 725 to 679 us and the bf16 forward pass at 8192 x 4096 -> 11008 from 725 to 693 us.  Launches of 128-row
-// tiles are not held back by power: against 32x32x16 MFMAs, activations first, they take 0 to 9 % less in bf16 and in the
-// forward pass, and between 2 % less and 2 % more in the fp16 backward pass.
+// register-resident loop on random fp16 operands sustains 1620 to 1660 TFLOP/s with 32x32x16 MFMAs and 1890 with 16x16x32
+// in the order used here (qlora_mfma_probe; half the accumulator traffic per flop).  The 16x16x32 form, weights as the
+// first operand and the MFMAs of a step in serpentine order take the fp16 step at 2048 x 4096 x 4096, INT4, from 153 to
+// 144 us, 4096 x 11008 -> 4096, INT3, from 725 to 679 us and the bf16 forward pass at 8192 x 4096 -> 11008 from 725 to
+// 693 us.  Launches of 128-row tiles are not held back by power: against 32x32x16 MFMAs, activations first, they take 0 to
+// 9 % less in bf16 and in the forward pass, and between 2 % less and 2 % more in the fp16 backward pass.
 // Launches that give every compute unit at least one 256 x 256 tile use a second arrangement of the same parts
 // (SYM below): eight waves that each stage, load and multiply an eighth.
 #include "common.hpp"
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     // The weight is the MFMA's first operand: a lane then holds four neighbouring output columns of one token row.  The
     // order of a step's MFMAs is a serpentine, so that each shares one operand with the one before: what the matrix
     // pipe draws, and with it the clock, follows how many operand bits change (register-resident loop on random fp16
-    // operands: 1835 TFLOP/s in plain order, 1934 as a serpentine).  Launches of 128-row tiles are not held back by power, and
+    // operands, one box: 1835 TFLOP/s in plain order, 1934 as a serpentine).  Launches of 128-row tiles are not held back by power, and
     // in plain order a step's first MFMAs need the fragments that arrive first (backward pass 2 % faster than as a serpentine).
     auto mfma_step = [&](int half, const AFrags &fa, const BFrags &fb) {
 #pragma unroll

@@ -34,13 +34,13 @@ constexpr int fw_static(int ar) { return 16 * (fw_tc(ar) + 1) * 4; }
 constexpr int FW_RS = 20;
 constexpr int fw_red(int nb) { return FW_NW * (nb + 1) * 16 * FW_RS * 4; }
 
-// 64 columns of 8-bit codes are half a cache line of a row.  Asked for at different times, often by two waves, every line
-// was fetched twice.  So one wave takes both halves, and its weight rows are requested for two chunks at once ("pair"), in two
-// slots of their own; token and adapter rows come by the chunk.  16 tokens, rank 8, INT8: 28672 -> 8192 65.8 -> 58.1 us,
-// 13824 -> 5120 29.3 -> 26.4; the two chunks dealt to one wave but requested apart took as long as before.  (2- and 4-bit
-// codes, rank 16: 12 to 16 % less at K = 28672, but 6 to 9 % more up to K = 384, where half of the waves get no
-// columns: not done.)  Three blocks leave room for too few of them (one token, 4096 -> 11008: 14.1 us apart, 15.1 in pairs), two
-// groups would need a third slot.
+// 64 columns of 8-bit codes are half a cache line of a row, and a request of half lines is as many lines to work through for
+// the compute unit as one of whole lines (HBM sees every line once: L2 has the other half).  So one wave takes both halves,
+// and its weight rows are requested for two chunks at once ("pair"), in two slots of their own; token and adapter rows come
+// by the chunk.  16 tokens, rank 8, INT8: 28672 -> 8192 65.8 -> 58.1 us, 13824 -> 5120 29.3 -> 26.4; the two chunks dealt to
+// one wave but requested apart took as long as before.  (2- and 4-bit codes, rank 16: 12 to 16 % less at K = 28672, but
+// 6 to 9 % more up to K = 384, where half of the waves get no columns: not done.)  Three blocks leave room for too few
+// pairs (one token, 4096 -> 11008: 14.1 us apart, 15.1 in pairs), two groups would need a third slot.
 constexpr int fw_wbytes(int bits, int nb, int ar, int xr) { return nb * 16 * fw_ks(bits, nb, ar, xr) * bits / 8; }
 constexpr int fw_pair_depth(int bits, int nb, int ar, int xr)       // chunks of token and adapter rows beside two pairs
 {
