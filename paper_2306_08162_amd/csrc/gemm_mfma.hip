@@ -326,16 +326,18 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     constexpr int EXT_A = BM * 2 / NSTG, EXT_W = BN * 2 / NSTG;   // pieces per staging thread and LoRA step
     u16x8_t ext_a[EXT_STEPS][EXT_A], ext_w[EXT_STEPS][EXT_W];
 
-    // Where unit i of this thread lies in stage kt: weight row n and first column k0.  TRANS: 64 contraction rows n,
-    // BN/32 units across the output columns k; else BN output rows n, 2 units along the contraction k.
-    auto unit_row = [&](int kt, int i) {
-        const int u = stid + NSTG * i;
-        return TRANS ? (kt_first + kt) * BK + (u & 63) : col0 + (u >> 1);
-    };
-    auto unit_col = [&](int kt, int i) {
-        const int u = stid + NSTG * i;
-        return TRANS ? col0 + (u >> 6) * 32 : (kt_first + kt) * BK + (u & 1) * 32;
-    };
+    // Where the unit of this thread lies in stage kt: weight row n and first column k0.  TRANS: 64 contraction rows n,
+    // UPR units across the output columns k; else BN output rows n, 2 units along the contraction k.
+    // TRANS: a wave takes all units of 64 / UPR rows, eight rows to eight neighbouring lanes (what the stage's writes need),
+    // so that one of its loads touches 16 rows (BN = 256: 8), not 64: the compute unit works through a load row by
+    // row, and the activation requests queue behind it.  Against one unit of each of the stage's 64 rows per wave, the whole
+    // backward pass, us: 600 x 4096 <- 11008, INT4, fp16 112 -> 103; 777 x 4096 <- 4096, bf16 52.6 -> 48.9; 2048 x 4096 <- 4096,
+    // INT8 82.0 -> 77.4; 4096 x 11008 <- 4096, INT8 377 -> 363.
+    static_assert(WU == 1, "one unit per staging thread and stage");
+    constexpr int UPR = BN / 32;
+    const int t_row = (stid >> 6) * (64 / UPR) + (stid & 63) / (8 * UPR) * 8 + (stid & 7), t_unit = (stid >> 3) % UPR;
+    auto unit_row = [&](int kt, int i) { return TRANS ? (kt_first + kt) * BK + t_row : col0 + (stid >> 1); };
+    auto unit_col = [&](int kt, int i) { return TRANS ? col0 + t_unit * 32 : (kt_first + kt) * BK + (stid & 1) * 32; };
     // global -> registers for stage kt.  Branch-free: every address is clamped into the valid range and
     // whatever lies beyond the contraction length (or beyond the weight's rows / columns) is neutralised by a
     // zero scale, so stages past the end may be fetched and staged harmlessly.  SYM: a uniform base and one register per
@@ -378,7 +380,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         if constexpr (TIGHT) asm volatile("" : "+v"(sr), "+v"(zr));      // not kept from one part to the next
         dq.set(ok ? f16_bits_to_f32((uint16_t)sr) : 0.f, (float)zr);
         uint32_t at;                                // byte offset of piece 0 in the stage
-        if constexpr (TRANS) at = (u & 63) * (WPITCH * 2) + ((((u >> 6) * 4) ^ wswz(u & 63)) * 16);
+        if constexpr (TRANS) at = t_row * (WPITCH * 2) + (((t_unit * 4) ^ wswz(t_row)) * 16);
         else if constexpr (SYM) at = (u >> 1) * (WPITCH * 2) + ((((u & 1) * 4) ^ fswz(u >> 1)) * 16);   // row u / 2
         else at = (u >> 1) * (WPITCH * 2) + (u & 1) * 64;
         if constexpr (SYM) asm("" : "+v"(at));      // the four addresses are formed when needed: four registers fewer
