@@ -60,3 +60,14 @@ def test_graph_replays_match_eager(M, K):
         torch.cuda.synchronize()
         for a, b in zip(eager, _snapshot(layer, sib)):
             assert np.array_equal(a, b), f"replay {rep} differs from the eager result"
+
+
+@pytest.mark.gpu
+def test_calls_follow_torchs_current_stream():
+    from paper_2306_08162_amd import binding as ql
+    side = torch.cuda.Stream()
+    for _ in range(2):                          # before and after the binding keeps torch's getters
+        assert (ql._stream(None) or 0) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert (ql._stream(None) or 0) == side.cuda_stream
+    assert (ql._stream(None) or 0) == torch.cuda.current_stream().cuda_stream
