@@ -85,8 +85,10 @@ size_t qlora_packed_words(int N, int K, int bits);
  * to 32 token rows the per-slice partial sums of u and dX of the
  * weight-streaming backward kernels, and, for token counts whose output makes
  * too few tiles to occupy the chip, the fp32 partial products of a GEMM whose
- * contraction is split over several workgroups (all summed in a fixed order,
- * so results are bitwise reproducible run to run).
+ * contraction is split over several workgroups, and beside those the partial
+ * sums of t or u at ranks 8 and 16 (all summed in a fixed order, so results are
+ * bitwise reproducible run to run).  A buffer that lacks the room for these last
+ * ones only is accepted too; t and u then come from launches of their own.
  */
 size_t qlora_workspace_bytes(int M, int N, int K, int bits, int group_size, int rank);
 

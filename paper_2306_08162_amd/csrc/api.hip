@@ -49,7 +49,9 @@ int check_problem(int M, int N, int K, int bits, int G, int r, int dtype)
 }
 
 struct Workspace {
-    size_t t_off, u_off, upartial_off, partial_off, split_off, total;
+    size_t t_off, u_off, upartial_off, partial_off, split_off, side_off, total;
+    size_t base_total;  // without the partial sums of t and u (side_off): a buffer of that size is accepted too, t and u
+                        // then come from launches of their own
     bool t_planes;      // the partial-dX region may serve as the fp32 planes of t = x A^T at small token counts: it holds
                         // at least M * K floats, the planes at most ceil(K / 128) * M * 64 of them (K >= 128: no more
                         // than that), and t is formed before anything else uses the region
@@ -74,6 +76,11 @@ Workspace carve(int M, int N, int K, int r, int bits)
     const size_t sf = (size_t)gemm_splits(M, N, K), sb = (size_t)gemm_splits(M, K, N);
     const size_t pf = sf > 1 ? sf * M * N * sizeof(float) : 0, pb = sb > 1 ? sb * M * K * sizeof(float) : 0;
     off += round_up(pf > pb ? pf : pb);
+    w.base_total = off < ALIGN ? ALIGN : off;
+    w.side_off = off;               // partial sums of t or u formed beside such a GEMM
+    const size_t ef = M > SMALL_M_FWD_MAX ? gemm_side_floats(M, N, K, r, true) : 0,
+                 eb = M > 16 ? gemm_side_floats(M, K, N, r, false) : 0;
+    off += round_up((ef > eb ? ef : eb) * sizeof(float));
     w.total = off < ALIGN ? ALIGN : off;
     w.t_planes = M <= SMALL_M_BWD_MAX && M <= LORA_DOWN_SMALL_MAX_M && K >= 128;    // (K >= 128: see Workspace)
     return w;
@@ -295,7 +302,7 @@ static int forward(const void *x, const uint32_t *packed, const void *scales, co
     if (misaligned(x) || misaligned(packed) || misaligned(scales) || misaligned(zeros) || misaligned(y) ||
         misaligned(A) || misaligned(B) || misaligned(t_save) || misaligned(ws) || misaligned(keep_mask))
         return QLORA_E_ALIGN;
-    if (!ws || ws_bytes < w.total) return QLORA_E_WORKSPACE;
+    if (!ws || ws_bytes < w.base_total) return QLORA_E_WORKSPACE;
     if (rank == 0) keep_mask = nullptr;         // no adapter branch: nothing is dropped
 
     const hipStream_t s = (hipStream_t)stream;
@@ -318,13 +325,16 @@ static int forward(const void *x, const uint32_t *packed, const void *scales, co
         void *t = nullptr;
         mark_pre_begin(s);
         if (zpacked) launch_unpack_zeros(zpacked, zscratch, N, K / group_size, bits, s);
-        if (rank > 0) {
+        // a GEMM whose contraction is split forms t itself, for the kernel that sums its planes
+        const bool side = !keep_mask && ws_bytes >= w.total && gemm_side_floats(M, N, K, rank, true) > 0;
+        if (rank > 0 && !side) {
             t = t_save ? t_save : (void *)(ws + w.t_off);
             launch_lora_down(x, A, t, M, K, rank, p.bf16, keep_mask, keep_scale, s);
         }
         mark_pre_end(s);
         GemmTimer timer(s, true);
-        launch_fwd_mfma(p, x, packed, scales, zeros, t, B, y, (float *)(ws + w.split_off), s);
+        launch_fwd_mfma(p, x, packed, scales, zeros, t, B, y, (float *)(ws + w.split_off), s, A, side ? t_save : nullptr,
+                        side ? (float *)(ws + w.side_off) : nullptr);
     }
     return end_call();
 }
@@ -373,7 +383,10 @@ Workspace carve_forward(int M, int N, int K, int r)
     w.t_off = 0;
     w.split_off = round_up((size_t)M * r * 2);
     const size_t sf = (size_t)gemm_splits(M, N, K);
-    w.total = w.split_off + (M > SMALL_M_FWD_MAX && sf > 1 ? round_up(sf * M * N * sizeof(float)) : 0);
+    const bool tiled = M > SMALL_M_FWD_MAX;
+    w.side_off = w.split_off + (tiled && sf > 1 ? round_up(sf * M * N * sizeof(float)) : 0);
+    w.base_total = w.side_off < ALIGN ? ALIGN : w.side_off;
+    w.total = w.side_off + (tiled ? round_up(gemm_side_floats(M, N, K, r, true) * sizeof(float)) : 0);
     if (w.total < ALIGN) w.total = ALIGN;
     return w;
 }
@@ -387,7 +400,7 @@ int qlora_linear_fwd_static(const void *x, const uint32_t *packed, const void *s
     const int st = check_problem(M, N, K, bits, group_size, rank, dtype);
     if (st != QLORA_OK) return st;
     const Workspace w = carve_forward(M, N, K, rank);
-    if (w.total > (size_t)QLORA_STATIC_SCRATCH_BYTES) return QLORA_E_STATIC;   // before anything touches the device
+    if (w.base_total > (size_t)QLORA_STATIC_SCRATCH_BYTES) return QLORA_E_STATIC;   // before anything touches the device
     void *ws = static_scratch();
     if (!ws) return QLORA_E_HIP;
     return forward(x, packed, scales, zeros, A, B, nullptr, 1.f, y, t_save, M, N, K, bits, group_size, rank, alpha,
@@ -431,7 +444,7 @@ static int backward(const void *dy, const void *x, const uint32_t *packed, const
         misaligned(workspace) || misaligned(keep_mask))
         return QLORA_E_ALIGN;
     const Workspace w = carve(M, N, K, rank, bits);
-    if (!workspace || workspace_bytes < w.total) return QLORA_E_WORKSPACE;
+    if (!workspace || workspace_bytes < w.base_total) return QLORA_E_WORKSPACE;
     if (rank == 0) keep_mask = nullptr;
 
     const hipStream_t s = (hipStream_t)stream;
@@ -470,9 +483,11 @@ static int backward(const void *dy, const void *x, const uint32_t *packed, const
     void *u = nullptr;
     mark_pre_begin(s);
     if (zpacked && !unpacked) launch_unpack_zeros(zpacked, zscratch, N, K / group_size, bits, s);
+    // as in forward(): a GEMM whose contraction is split forms u itself
+    const bool side = !keep_mask && workspace_bytes >= w.total && gemm_side_floats(M, K, N, rank, false) > 0;
     if (rank > 0) {
         u = ws + w.u_off;
-        launch_lora_u(dy, B, u, M, N, rank, p.bf16, s);
+        if (!side) launch_lora_u(dy, B, u, M, N, rank, p.bf16, s);
     }
     mark_pre_end(s);
     {
@@ -486,7 +501,7 @@ static int backward(const void *dy, const void *x, const uint32_t *packed, const
                                1.f, s);
         } else {                // keep_mask: the GEMM's epilogue adds the adapter's share masked per element
             launch_bwd_dx_mfma(p, dy, packed, scales, zeros, u, A, dx, (float *)(ws + w.split_off), keep_mask, keep_scale,
-                               s);
+                               s, B, u, side ? (float *)(ws + w.side_off) : nullptr);
         }
     }
     if (keep_mask && rank > GEMM_MASKED_MAX_RANK)
@@ -549,9 +564,11 @@ int qlora_linear_fwd_zp(const void *x, const uint32_t *packed, const void *scale
     if (st != QLORA_OK) return st;
     if (!packed_zeros) return QLORA_E_NULL;
     const Workspace w = carve(M, N, K, rank, bits);
-    if (!workspace || workspace_bytes < w.total + round_up((size_t)N * (K / group_size))) return QLORA_E_WORKSPACE;
+    const size_t zbytes = round_up((size_t)N * (K / group_size));
+    if (!workspace || workspace_bytes < w.base_total + zbytes) return QLORA_E_WORKSPACE;
+    const size_t room = workspace_bytes < w.total + zbytes ? w.base_total : w.total;
     return forward(x, packed, scales, nullptr, A, B, nullptr, 1.f, y, t_save, M, N, K, bits, group_size, rank, alpha,
-                   dtype, (char *)workspace, w, w.total, stream, packed_zeros, (uint8_t *)workspace + w.total);
+                   dtype, (char *)workspace, w, room, stream, packed_zeros, (uint8_t *)workspace + room);
 }
 
 int qlora_linear_bwd_zp(const void *dy, const void *x, const uint32_t *packed, const void *scales,
@@ -563,10 +580,12 @@ int qlora_linear_bwd_zp(const void *dy, const void *x, const uint32_t *packed, c
     if (st != QLORA_OK) return st;
     if (!packed_zeros) return QLORA_E_NULL;
     const Workspace w = carve(M, N, K, rank, bits);
-    if (!workspace || workspace_bytes < w.total + round_up((size_t)N * (K / group_size))) return QLORA_E_WORKSPACE;
+    const size_t zbytes = round_up((size_t)N * (K / group_size));
+    if (!workspace || workspace_bytes < w.base_total + zbytes) return QLORA_E_WORKSPACE;
+    const size_t room = workspace_bytes < w.total + zbytes ? w.base_total : w.total;
     return backward(dy, x, packed, scales, nullptr, A, B, nullptr, 1.f, t_saved, dx, dA, dB, beta, 0, M, N, K, bits,
-                    group_size, rank, alpha, dtype, workspace, w.total, stream, packed_zeros,
-                    (uint8_t *)workspace + w.total);
+                    group_size, rank, alpha, dtype, workspace, room, stream, packed_zeros,
+                    (uint8_t *)workspace + room);
 }
 
 namespace {

@@ -49,6 +49,10 @@ struct GemmArgs {
     int splits, kt_split;     // workgroups per tile along the contraction, 64-deep stages per workgroup
     const uint8_t *keep;      // LoRA dropout (backward only): keep bit of x[m, k] is bit k % 8 of keep[m * K/8 + k/8]
     float keep_sc;            // sc * keep_scale
+    // split contraction: t (or u) formed beside the GEMM, see "side product"; side_r == 0: it is not
+    const uint16_t *side_w;   // A [r,K] (forward) or B [N,r] (backward)
+    float *side;              // partial sums [M][splits * side_p][side_r]
+    int side_r, side_p;       // side_p: workgroups of a tile row and split that hold some
 };
 
 template <bool BF16>
@@ -125,7 +129,10 @@ __device__ __forceinline__ constexpr int fswz(int row) { return ((row & 3) ^ ((r
 // MFMAs.  The accumulators are half of a wave's 256 registers; a spilled register would be reloaded through the
 // vector-memory counter that the stages wait on (a build with a dozen spills took 1.4 times as long), so addresses are
 // formed when they are needed, two sets of packed words are in flight and two block rows of fragments are held.
-template <int BITS, bool BF16, bool TRANS, int BM, int BN, int WM, int WN, bool MASKED = false, bool SYM = false>
+//
+// SIDE (launches of 128-row tiles whose contraction is split): t (forward) or u (backward) is formed as well, see "side
+// product".  A template argument: a branch that is never taken cost the unsplit launches 1 to 4 %.
+template <int BITS, bool BF16, bool TRANS, int BM, int BN, int WM, int WN, bool MASKED = false, bool SYM = false, bool SIDE = false>
 __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kernel(const GemmArgs a)
 {
     static_assert(!MASKED || TRANS, "the dropout mask acts on dX only");
@@ -162,6 +169,9 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     constexpr int WPITCH = TRANS ? BN : (SYM ? BK : LDS_STRIDE);
     constexpr int WS = TRANS ? BK * WPITCH : BN * WPITCH;       // halfs per weight stage
     using Regs = StageRegs<BITS, WU>;
+
+    static_assert(!SIDE || (BM == 128 && !SYM && !MASKED), "launches whose contraction is split");
+    constexpr int SIDE_I = MI / WN;                 // side product: block rows per wave
 
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     uint16_t *const xs = smem;                      // [NXS][BM][64]
@@ -298,6 +308,10 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     constexpr int A_READS = MH, B_READS = TRANS ? 2 * NI : NI;
     AFrags fa[2];
     BFrags fb[2];
+    [[maybe_unused]] u16x8_t sf[BK / 32];           // side product: the small operand's fragments of one stage
+    [[maybe_unused]] float4_t sacc[SIDE_I];
+#pragma unroll
+    for (int i = 0; i < SIDE_I; ++i) sacc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
     // The steps of one stage.  `work(s)` runs before step s's MFMAs are issued (loads, staging), `turn()` between the
     // last but one step and the last: the wait and barrier behind which the next stage's fragments may be read; the
     // last step runs from registers, over the LDS latency of those.
@@ -476,6 +490,35 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
             const uint32_t dst = xs_lds + (uint32_t)(stage * XS + (MW * i + cw) * 512) * 2u;   // wave-uniform byte address
             dma16(a.act, xoff[i] + k2, (uint32_t)__builtin_amdgcn_readfirstlane((int)dst));
         };
+        // Side product: the workgroups of a tile row all hold the same activation stages, so each of them multiplies some by
+        // the small operand as well (stages pn, pn + tiles_n, ... of its run), a half of the tile's rows per wave column, and
+        // leaves fp32 partial sums of t (or u) that the kernel which sums the planes adds up.  That is a launch less than with t
+        // (or u) by a kernel of its own, which took 5 to 6 us beside 20 of the GEMM.  INT2, fp16, rank 8, forward / backward, us:
+        // 64 x 4096 <- 4096 20.8 -> 18.6 / 24.9 -> 20.4; 256 30.3 -> 28.3 / 33.2 -> 28.8; 512 x 4096 <- 11008 74.0 -> 67.4 / 67.4 -> 65.2.
+        [[maybe_unused]] int side_kt = SIDE && pn < a.side_p ? pn : KT;
+        auto side_load = [&](int kt) {
+#pragma unroll
+            for (int ks = 0; ks < BK / 32; ++ks) {
+                const int k = (kt_first + kt) * BK + 32 * ks + 8 * fq;          // eight contraction elements of this lane
+                const bool in = k < KC;
+                sf[ks] = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
+                if (!in || fr >= a.side_r) continue;
+                if constexpr (TRANS) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sf[ks][e] = a.side_w[(long)(k + e) * a.side_r + fr];
+                } else sf[ks] = *(const u16x8_t *)(a.side_w + (long)fr * a.K + k);
+            }
+        };
+        auto side_step = [&](int xstage) {
+#pragma unroll
+            for (int ks = 0; ks < BK / 32; ++ks)
+#pragma unroll
+                for (int i = 0; i < SIDE_I; ++i) {
+                    const u16x8_t x = *(const u16x8_t *)(xs + xstage * XS + aoff[ks] + (wn * SIDE_I + i) * 16 * BK);
+                    sacc[i] = mfma16<BF16>(sf[ks], x, sacc[i]);             // D[j = 4 fq + v][m = fr]
+                }
+        };
+        if (SIDE && side_kt < KT) side_load(side_kt);           // the oldest requests: they have landed with the first stage
 #pragma unroll
         for (int i = 0; i < XDMA; ++i) issue_x(0, 0, i);
         if constexpr (NXS == 3) {
@@ -484,6 +527,10 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         }
         constexpr int AHEAD = NXS == 3 ? XDMA : 0;   // loads that may still be in flight when a stage is needed
         wait_vm_and_barrier<AHEAD>();           // stage 0 of the activations has landed; weights staged by waves 4-7
+        if constexpr (SIDE) {
+#pragma unroll
+            for (int ks = 0; ks < BK / 32; ++ks) asm volatile("" : "+v"(sf[ks]));     // the compiler's wait for them goes here
+        }
         load_a(0, 0, 0, fa[0]);
         load_b(0, 0, fb[0]);
         int xstage = 0;                         // kt % NXS
@@ -496,6 +543,11 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                 for (int i = st * XDMA / STEPS; i < (st + 1) * XDMA / STEPS; ++i) issue_x(kt + NXS - 1, xfill, i);
             };
             auto turn = [&]() { wait_vm_and_barrier<AHEAD>(); };   // stage kt+1 has landed (only loads for a later one may be pending)
+            if (SIDE && kt == side_kt) {
+                side_step(xstage);
+                side_kt += a.tiles_n;
+                if (side_kt < KT) side_load(side_kt);
+            }
             stage_steps(xstage, kt & 1, xnext, work, turn);
             xstage = xnext;
         }
@@ -664,6 +716,14 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                     const int grow = row0 + wm * TM + i * 16 + (lane & 15), gcol = col0 + wn * TN + j * 16 + (lane >> 4) * 4;
                     if (grow < a.M && gcol < NO) *(float4_t *)(P + (size_t)grow * NO + gcol) = acc[i][j];   // NO % 8 == 0
                 }
+            if (SIDE && pn < a.side_p) {
+#pragma unroll
+                for (int i = 0; i < SIDE_I; ++i) {
+                    const int m = row0 + wm * TM + (wn * SIDE_I + i) * 16 + fr, j = 4 * fq;
+                    if (m < a.M && j < a.side_r)
+                        *(float4_t *)(a.side + ((size_t)m * (a.splits * a.side_p) + split * a.side_p + pn) * a.side_r + j) = sacc[i];
+                }
+            }
         }
         return;
     }
@@ -718,7 +778,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     }
 }
 
-template <int BITS, bool BF16, bool TRANS, int BM, int BN, int WM, int WN, bool MASKED = false, bool SYM = false>
+template <int BITS, bool BF16, bool TRANS, int BM, int BN, int WM, int WN, bool MASKED = false, bool SYM = false, bool SIDE = false>
 void launch_variant(const GemmArgs &a, hipStream_t s)
 {
     constexpr size_t wstage = TRANS ? (size_t)BK * BN : (size_t)BN * (SYM ? BK : LDS_STRIDE);
@@ -727,7 +787,7 @@ void launch_variant(const GemmArgs &a, hipStream_t s)
     constexpr size_t lds_epi = (size_t)WM * WN * (BM / WM) * (BN / WN + 8) * sizeof(uint16_t) + lds_side;
     constexpr size_t lds = lds_pipe > lds_epi ? lds_pipe : lds_epi;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    auto kern = qgemm_kernel<BITS, BF16, TRANS, BM, BN, WM, WN, MASKED, SYM>;
+    auto kern = qgemm_kernel<BITS, BF16, TRANS, BM, BN, WM, WN, MASKED, SYM, SIDE>;
     ensure_dynamic_lds((const void *)kern, (int)(lds));
     QLORA_LAUNCH(kern, dim3(a.tiles_m * a.tiles_n * a.splits), dim3(WM * WN * 64 + (SYM ? 0 : STAGERS)), lds, s, a);
 }
@@ -750,6 +810,93 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float *__restrict
     *(u16x4_t *)(out + e) = u16x4_t{to16<BF16>(acc[0]), to16<BF16>(acc[1]), to16<BF16>(acc[2]), to16<BF16>(acc[3])};
 }
 
+// The same sum where t (or u) was formed beside the GEMM: SIDE_ROWS token rows and 1024 columns per workgroup.  Their partial
+// sums of t are added first, rounded as t is, written once (by the first column block) and multiplied with B [N, R]
+// (forward) or A [R, K] (backward); sc * t is rounded to 16 bits, as in the extra contraction steps of an unsplit GEMM.
+// Bound by the latency of its chain (partial sums, barrier, t, barrier) and the planes' bytes; the planes are requested ahead of
+// the partial sums.  B is read once for the SIDE_ROWS rows, the partial sums, a few KB per row, by every column block.  One row
+// per workgroup instead of two: 256 x 4096 <- 4096, rank 8 28.3 -> 27.5 us, but 64 rows 18.6 -> 19.9; four: 29.6 and 21.2.
+constexpr int SIDE_ROWS = 2;
+struct SideSum {
+    const float *part, *side;
+    const uint16_t *w;        // B (forward) or A (backward)
+    uint16_t *out, *t;        // t may be NULL
+    int M, NO, P;             // P: partial sums of t per token row
+    float sc;
+};
+template <bool BF16, bool TRANS, int S, int R>
+__global__ __launch_bounds__(256) void splitk_sum_side_kernel(const SideSum a)
+{
+    __shared__ float red[SIDE_ROWS][4][R], st[SIDE_ROWS][R];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m0 = blockIdx.y * SIDE_ROWS, col = (blockIdx.x * 256 + tid) * 4;
+    const bool live = col < a.NO;
+    const size_t plane = (size_t)a.M * a.NO;
+    float4_t p[SIDE_ROWS][S];
+#pragma unroll
+    for (int i = 0; i < SIDE_ROWS; ++i)
+#pragma unroll
+        for (int sp = 0; sp < S; ++sp)
+            if (live) p[i][sp] = *(const float4_t *)(a.part + sp * plane + (size_t)min(m0 + i, a.M - 1) * a.NO + col);
+    u16x8_t wf[TRANS ? 1 : 4 * R / 8];
+    u16x4_t wb[TRANS ? R : 1];
+    if (live) {
+        if constexpr (TRANS) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) wb[j] = *(const u16x4_t *)(a.w + (size_t)j * a.NO + col);
+        } else {
+#pragma unroll
+            for (int h = 0; h < 4 * R / 8; ++h) wf[h] = *(const u16x8_t *)(a.w + (size_t)col * R + 8 * h);
+        }
+    }
+    const int n = a.P * R;
+#pragma unroll
+    for (int i = 0; i < SIDE_ROWS; ++i) {
+        const float *src = a.side + (size_t)min(m0 + i, a.M - 1) * n;
+        float v = 0.f;
+        for (int f = tid; f < n; f += 256) v += src[f];         // column f % R = tid % R
+#pragma unroll
+        for (int d = R; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
+        if (lane < R) red[i][wave][lane] = v;
+    }
+    __syncthreads();
+    if (tid < SIDE_ROWS * R) {
+        const int i = tid / R, j = tid % R;
+        const uint16_t t = to16<BF16>(red[i][0][j] + red[i][1][j] + red[i][2][j] + red[i][3][j]);
+        if (a.t && blockIdx.x == 0 && m0 + i < a.M) a.t[(size_t)(m0 + i) * R + j] = t;
+        st[i][j] = cvt16<BF16>(to16<BF16>(a.sc * cvt16<BF16>(t)));
+    }
+    __syncthreads();
+    if (!live) return;
+#pragma unroll
+    for (int i = 0; i < SIDE_ROWS; ++i) {
+        if (m0 + i >= a.M) return;
+        float4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sp = 0; sp < S; ++sp) acc += p[i][sp];
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                acc[c] = fmaf(st[i][j], cvt16<BF16>(TRANS ? wb[TRANS ? j : 0][c] : wf[TRANS ? 0 : (c * R + j) / 8][j & 7]), acc[c]);
+        *(u16x4_t *)(a.out + (size_t)(m0 + i) * a.NO + col) =
+            u16x4_t{to16<BF16>(acc[0]), to16<BF16>(acc[1]), to16<BF16>(acc[2]), to16<BF16>(acc[3])};
+    }
+}
+
+template <bool BF16, bool TRANS, int S>
+void launch_splitk_sum_side(const SideSum &a, int r, hipStream_t s)      // gemm_side_floats(): r is 8, backward 16 too
+{
+    const dim3 grid((unsigned)((a.NO / 4 + 255) / 256), (unsigned)((a.M + SIDE_ROWS - 1) / SIDE_ROWS)), block(256);
+    if constexpr (TRANS) {
+        if (r == 16) {
+            QLORA_LAUNCH((splitk_sum_side_kernel<BF16, TRANS, S, 16>), grid, block, 0, s, a);
+            return;
+        }
+    }
+    QLORA_LAUNCH((splitk_sum_side_kernel<BF16, TRANS, S, 8>), grid, block, 0, s, a);
+}
+
 template <bool BF16>
 void launch_splitk_sum(const float *part, uint16_t *out, size_t plane, int splits, hipStream_t s)
 {
@@ -766,7 +913,7 @@ void launch_splitk_sum(const float *part, uint16_t *out, size_t plane, int split
 }
 
 template <int BITS, bool BF16, bool TRANS>
-void launch_tiles(GemmArgs &a, hipStream_t s)
+void launch_tiles(GemmArgs &a, uint16_t *side_out, hipStream_t s)
 {
     constexpr int BM = 256, BN = 128, WM = 2, WN = 2;       // tile shape and grid of MFMA waves
     static_assert(BN == GEMM_SPLIT_BN, "gemm_splits() counts tiles of this width");
@@ -795,6 +942,21 @@ void launch_tiles(GemmArgs &a, hipStream_t s)
             if (splits > 1) {
                 a.splits = splits;
                 a.kt_split = (a.kt_split + splits - 1) / splits;
+            }
+            if (splits > 1 && a.side_r > 0) {
+                a.side_p = min(a.tiles_n, a.kt_split);
+                launch_variant<BITS, BF16, TRANS, 128, BN, WM, WN, false, false, true>(a, s);
+                const SideSum q{a.part, a.side, a.ext_w, a.out, side_out, a.M, NO, splits * a.side_p, a.sc};
+                switch (splits) {
+                case 2: launch_splitk_sum_side<BF16, TRANS, 2>(q, a.side_r, s); break;
+                case 3: launch_splitk_sum_side<BF16, TRANS, 3>(q, a.side_r, s); break;
+                case 4: launch_splitk_sum_side<BF16, TRANS, 4>(q, a.side_r, s); break;
+                case 5: launch_splitk_sum_side<BF16, TRANS, 5>(q, a.side_r, s); break;
+                case 6: launch_splitk_sum_side<BF16, TRANS, 6>(q, a.side_r, s); break;
+                case 7: launch_splitk_sum_side<BF16, TRANS, 7>(q, a.side_r, s); break;
+                default: launch_splitk_sum_side<BF16, TRANS, 8>(q, a.side_r, s); break;
+                }
+                return;
             }
             launch_variant<BITS, BF16, TRANS, 128, BN, WM, WN>(a, s);
             if (splits > 1) launch_splitk_sum<BF16>(a.part, a.out, (size_t)a.M * NO, splits, s);
@@ -831,20 +993,20 @@ inline uint32_t group_magic(int G)
 }
 
 template <bool TRANS>
-void launch_bits_dtype(const Problem &p, GemmArgs &a, hipStream_t s)
+void launch_bits_dtype(const Problem &p, GemmArgs &a, uint16_t *side_out, hipStream_t s)
 {
 #define QLORA_CASE(B)                                   \
     case B:                                             \
-        if (p.bf16) launch_tiles<B, true, TRANS>(a, s); \
-        else launch_tiles<B, false, TRANS>(a, s);       \
+        if (p.bf16) launch_tiles<B, true, TRANS>(a, side_out, s); \
+        else launch_tiles<B, false, TRANS>(a, side_out, s);       \
         break
     switch (p.bits) {
         QLORA_CASE(2);
         QLORA_CASE(3);
         QLORA_CASE(4);
     default:
-        if (p.bf16) launch_tiles<8, true, TRANS>(a, s);
-        else launch_tiles<8, false, TRANS>(a, s);
+        if (p.bf16) launch_tiles<8, true, TRANS>(a, side_out, s);
+        else launch_tiles<8, false, TRANS>(a, side_out, s);
         break;
     }
 #undef QLORA_CASE
@@ -852,22 +1014,35 @@ void launch_bits_dtype(const Problem &p, GemmArgs &a, hipStream_t s)
 
 }  // namespace
 
+// The arguments of a launch whose t (or u) is formed beside the GEMM: the adapter takes no part in the GEMM itself
+static void take_side(GemmArgs &a, const void *side_w, float *side)
+{
+    a.side_w = (const uint16_t *)side_w;
+    a.side = side;
+    a.side_r = a.r;
+    a.r = 0;
+}
+
 void launch_fwd_mfma(const Problem &p, const void *x, const uint32_t *packed, const void *scales, const uint8_t *zeros,
-                     const void *t, const void *B, void *y, float *part, hipStream_t s)
+                     const void *t, const void *B, void *y, float *part, hipStream_t s, const void *A, void *t_out,
+                     float *side)
 {
     GemmArgs a{(const uint16_t *)x, packed, (const uint16_t *)scales, zeros, (const uint16_t *)t, (const uint16_t *)B,
-               (uint16_t *)y, p.M, p.N, p.K, p.G, p.r, p.sc, 0, 0, group_magic(p.G), part, 1, 0, nullptr, 0.f};
-    launch_bits_dtype<false>(p, a, s);
+               (uint16_t *)y, p.M, p.N, p.K, p.G, p.r, p.sc, 0, 0, group_magic(p.G), part, 1, 0, nullptr, 0.f,
+               nullptr, nullptr, 0, 0};
+    if (side) take_side(a, A, side);
+    launch_bits_dtype<false>(p, a, (uint16_t *)t_out, s);
 }
 
 void launch_bwd_dx_mfma(const Problem &p, const void *dy, const uint32_t *packed, const void *scales,
                         const uint8_t *zeros, const void *u, const void *A, void *dx, float *part,
-                        const uint32_t *keep, float keep_scale, hipStream_t s)
+                        const uint32_t *keep, float keep_scale, hipStream_t s, const void *B, void *u_out, float *side)
 {
     GemmArgs a{(const uint16_t *)dy, packed, (const uint16_t *)scales, zeros, (const uint16_t *)u, (const uint16_t *)A,
                (uint16_t *)dx, p.M, p.N, p.K, p.G, p.r, p.sc, 0, 0, group_magic(p.G), part, 1, 0,
-               p.r > 0 ? (const uint8_t *)keep : nullptr, p.sc * keep_scale};
-    launch_bits_dtype<true>(p, a, s);
+               p.r > 0 ? (const uint8_t *)keep : nullptr, p.sc * keep_scale, nullptr, nullptr, 0, 0};
+    if (side) take_side(a, B, side);
+    launch_bits_dtype<true>(p, a, (uint16_t *)u_out, s);
 }
 
 }  // namespace qlora

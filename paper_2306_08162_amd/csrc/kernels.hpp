@@ -83,16 +83,31 @@ inline int gemm_splits(int M, int NO, int KC)
     const int s = by_cus < by_depth ? by_cus : by_depth;
     return s > 8 ? 8 : (s < 1 ? 1 : s);
 }
+// Floats of the partial sums of t (forward) or u (backward) that a split launch of rank r forms beside the GEMM: up to
+// min(tile columns, stages of a split) per split and token row.  0: t or u comes from a launch of its own.  That is so for
+// higher ranks, whose partial sums and adapter rows cost the kernel that adds them more than the launch saved (64 x 5120 <- 13824,
+// rank 32, forward 40.3 -> 44.1 us; 257 x 2080 <- 4104, backward 31.3 -> 32.1), and for rank 16 forward, where a thread's four
+// rows of B are 128 bytes (512 x 4096 <- 4096: 36.6 -> 38.4, 256: 30.6 -> 29.5).
+inline size_t gemm_side_floats(int M, int NO, int KC, int r, bool forward)
+{
+    const int s = gemm_splits(M, NO, KC);
+    if (s < 2 || !(r == 8 || (r == 16 && !forward))) return 0;
+    const int tiles_n = (NO + GEMM_SPLIT_BN - 1) / GEMM_SPLIT_BN, kt = ((KC + 63) / 64 + s - 1) / s;
+    return (size_t)s * (tiles_n < kt ? tiles_n : kt) * M * r;
+}
 // part: gemm_splits(M, NO, KC) * M * NO floats when that count exceeds 1 (NO = N, KC = K forward; NO = K, KC = N
-// backward); NULL switches splitting off
+// backward); NULL switches splitting off.  side != NULL (gemm_side_floats() of them, more than 0): t = x A^T (u = dY B) is formed
+// by the launch itself and t (u) is not read; t_out (u_out), if not NULL, receives it.
 void launch_fwd_mfma(const Problem &p, const void *x, const uint32_t *packed, const void *scales,
-                     const uint8_t *zeros, const void *t, const void *B, void *y, float *part, hipStream_t s);
+                     const uint8_t *zeros, const void *t, const void *B, void *y, float *part, hipStream_t s,
+                     const void *A = nullptr, void *t_out = nullptr, float *side = nullptr);
 // keep != NULL (LoRA dropout, ranks up to GEMM_MASKED_MAX_RANK): dX = dY Wd + sc keep_scale keep (.) (u A), the
 // masked product added in the epilogue (the contraction is then never split)
 constexpr int GEMM_MASKED_MAX_RANK = 32;
 void launch_bwd_dx_mfma(const Problem &p, const void *dy, const uint32_t *packed, const void *scales,
                         const uint8_t *zeros, const void *u, const void *A, void *dx, float *part,
-                        const uint32_t *keep, float keep_scale, hipStream_t s);
+                        const uint32_t *keep, float keep_scale, hipStream_t s, const void *B = nullptr,
+                        void *u_out = nullptr, float *side = nullptr);
 
 // gemv.hip -- small token counts: weight-streaming kernels, one pass over the packed weight
 constexpr int SMALL_M_FWD_MAX = 32;   // above: the tiled GEMM with its contraction split over workgroups is faster

@@ -1,8 +1,10 @@
 """GPU parity of the tiled GEMM against the CPU oracle where its dispatch changes from 128- to 256-row tiles: one round of
-256 tiles of 128 x 128 (and one tile row or column more) in each direction, with and without the masked epilogue."""
+256 tiles of 128 x 128 (and one tile row or column more) in each direction, with and without the masked epilogue; and where
+it splits its contraction and forms t or u beside the GEMM."""
+import numpy as np
 import pytest
 
-from parity import check_layer, small_inputs
+from parity import announce, check_layer, rel_fro, small_inputs, unit_roundoff
 
 pytestmark = pytest.mark.gpu
 
@@ -16,3 +18,31 @@ CASES = [(M, K, N, bits, dtype)
 def test_tile_height_boundary(case):
     M, K, N, bits, dtype = case
     check_layer(small_inputs(M + 3 * K + N + bits, M, K, N, bits, 32, 8, dtype))
+
+
+# split contractions at ranks 8 and 16: fewer tile columns than stages of a split (33), a contraction that ends inside a stage
+# (2080, 1032), a last split shorter than the tile columns (4160), 8-bit codes at 28 tokens (tiled backward pass only)
+SIDE = [(33, 4096, 512, 4, 8, "f16"), (130, 2080, 1032, 3, 8, "bf16"), (40, 1024, 4160, 2, 16, "f16"),
+        (200, 1056, 2056, 2, 16, "bf16"), (28, 1024, 1024, 8, 8, "f16"), (129, 2048, 136, 8, 8, "f16")]
+
+
+@pytest.mark.parametrize("case", SIDE, ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(*c))
+def test_adapter_products_beside_a_split_gemm(case):
+    import torch
+    from paper_2306_08162_amd.device import DeviceLayer
+    M, K, N, bits, r, dtype = case
+    inp = small_inputs(M + K + N + bits, M, K, N, bits, 32, r, dtype)
+    check_layer(inp)
+    # a workspace without the room for the partial sums of t and u: they come from launches of their own.  Both forms round
+    # the same fp32 sums, taken in another order, to 16 bits: half a unit in the last place each
+    announce(f"smaller workspace: {inp.cfg.name}")
+    full, less = DeviceLayer(inp), DeviceLayer(inp)
+    less.workspace = less.workspace[:-256]
+    for layer in (full, less):
+        layer.forward()
+        layer.backward()
+    torch.cuda.synchronize()
+    import oracle
+    for name in ("host_y", "host_dx"):
+        a, b = (np.asarray(oracle.widen(getattr(l, name)(), dtype), np.float64) for l in (full, less))
+        assert rel_fro(a, b) <= unit_roundoff(dtype), name
