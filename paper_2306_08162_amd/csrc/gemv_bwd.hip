@@ -45,6 +45,15 @@ __device__ __forceinline__ uint32_t code_of(const uint32_t (&w)[WORDS], int c)
     return v & mask;
 }
 
+// (x & mask) | magic as one instruction: the mask from a scalar register, the magic from a vector register (the compiler takes
+// two: fp16, 16 tokens, gate and up INT2 23.9 -> 22.7 us, INT4 30.8 -> 30.2)
+__device__ __forceinline__ uint32_t rows_and_or(uint32_t x, uint32_t mask, uint32_t magic)
+{
+    uint32_t d;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "s"(mask), "v"(magic));
+    return d;
+}
+
 // fp16: column c of eight consecutive weight rows as one MFMA fragment (element e = row e).  Rows are handled in
 // pairs: one byte permute drops the code of both rows into the mantissas of (1024.0, 1024.0), at bit p of each
 // half; a packed fma with (2^-p, -(1024 * 2^-p + z)) leaves the exact integers q - z and a packed multiply applies
@@ -70,9 +79,54 @@ __device__ __forceinline__ u16x8_t dequant_rows8_f16(const uint32_t (&w)[8][WORD
             lo = __builtin_amdgcn_alignbit(w[2 * i][wi + 1 < WORDS ? wi + 1 : wi], lo, (uint32_t)sh);
             hi = __builtin_amdgcn_alignbit(w[2 * i + 1][wi + 1 < WORDS ? wi + 1 : wi], hi, (uint32_t)sh);
         }
-        const uint32_t bits = (__builtin_amdgcn_perm(hi, lo, sel) & mask2) | 0x64006400u;
+        const uint32_t bits = BITS == 8 ? __builtin_amdgcn_perm(hi, lo, sel) | 0x64006400u
+                                        : rows_and_or(__builtin_amdgcn_perm(hi, lo, sel), mask2, 0x64006400u);
         const half2_t h = __builtin_bit_cast(half2_t, bits);
         out[i] = __builtin_bit_cast(uint32_t, (h * mul2 + (nz2[i] + off2)) * s2[i]);
+    }
+    return __builtin_bit_cast(u16x8_t, out);
+}
+
+// bf16: column c of eight consecutive weight rows as one MFMA fragment.  Two rows' codes meet in the mantissas of
+// (1024.0, 1024.0) as above; one mixed-precision fma per code with the row's s * 2^-p and -(1024 * 2^-p + z) * s gives
+// s (q - z) exactly, rounded once.  8-bit codes: a byte conversion and one fma.  The kernel is bound by its instructions: 2.5
+// to 3 per code; extracting, converting, subtracting and scaling every code by itself took 5 (bf16, 16 tokens, whole
+// backward pass: gate and up INT2 30.1 -> 25.9 us, INT4 34.7 -> 32.1, INT8 36.5 -> 35.8; q INT2 14.9 -> 14.0).
+template <int BITS, int WORDS>
+struct RowsConst {
+    static constexpr int NP = BITS == 2 ? 4 : (BITS == 4 ? 2 : 1);      // positions p = BITS i of a code in its byte
+    float mul[NP][8], off[NP][8];
+    __device__ __forceinline__ void set(int e, float s, float z)
+    {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const float inv = 1.f / (float)(1 << (BITS * i));
+            mul[i][e] = s * inv;
+            off[i][e] = BITS == 8 ? -z * s : -(1024.f * inv + z) * s;
+        }
+    }
+};
+template <int BITS, int WORDS>
+__device__ __forceinline__ u16x8_t dequant_rows8_bf16(const uint32_t (&w)[8][WORDS], int c, const RowsConst<BITS, WORDS> &k)
+{
+    typedef float float2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    const int o = BITS * c, wi = o >> 5, bb = (o & 31) >> 3, p = o & 7, i = p / BITS;
+    u32x4_t out;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const uint32_t lo = w[2 * h][wi], hi = w[2 * h + 1][wi];
+        float2_t f;
+        if constexpr (BITS == 8) {
+            f = float2_t{__builtin_fmaf((float)((lo >> (8 * bb)) & 0xffu), k.mul[0][2 * h], k.off[0][2 * h]),
+                         __builtin_fmaf((float)((hi >> (8 * bb)) & 0xffu), k.mul[0][2 * h + 1], k.off[0][2 * h + 1])};
+        } else {
+            const uint32_t sel = (uint32_t)bb | 0x0C00u | ((uint32_t)(4 + bb) << 16) | 0x0C000000u, m1 = ((1u << BITS) - 1u) << p;
+            const half2_t v = __builtin_bit_cast(half2_t, rows_and_or(__builtin_amdgcn_perm(hi, lo, sel), m1 | (m1 << 16), 0x64006400u));
+            f = float2_t{__builtin_fmaf((float)v[0], k.mul[i][2 * h], k.off[i][2 * h]),
+                         __builtin_fmaf((float)v[1], k.mul[i][2 * h + 1], k.off[i][2 * h + 1])};
+        }
+        out[h] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
     }
     return __builtin_bit_cast(u16x8_t, out);
 }
@@ -452,17 +506,13 @@ __device__ __forceinline__ void gemv_bwd_staged_body(const BwdArgs &a, const int
         const u32x4_t sv = __builtin_bit_cast(u32x4_t, *(const u16x8_t *)cs);
         const u32x4_t zv = __builtin_bit_cast(u32x4_t, *(const u16x8_t *)(cs + 2 * BS_RS));
         if constexpr (BF16) {
-            float s[8], z[8];
+            RowsConst<BITS, WORDS> k;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                s[e] = f16_bits_to_f32((uint16_t)(sv[e >> 1] >> (16 * (e & 1))));
-                z[e] = -f16_bits_to_f32((uint16_t)(zv[e >> 1] >> (16 * (e & 1))));
-            }
+            for (int e = 0; e < 8; ++e)
+                k.set(e, f16_bits_to_f32((uint16_t)(sv[e >> 1] >> (16 * (e & 1)))), -f16_bits_to_f32((uint16_t)(zv[e >> 1] >> (16 * (e & 1)))));
 #pragma unroll
             for (int c = 0; c < CL; ++c) {
-                u16x8_t wf;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) wf[e] = to16<BF16>(((float)code_of<BITS, WORDS>(w[e], c) - z[e]) * s[e]);
+                const u16x8_t wf = dequant_rows8_bf16<BITS, WORDS>(w, c, k);
 #pragma unroll
                 for (int b = 0; b < MB; ++b) acc[b][c] = mfma16<BF16>(df[b], wf, acc[b][c]);   // D[m = 4q+v][column CL wc + c]
             }
