@@ -336,6 +336,58 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         }
     };
 
+    // The same in pieces of one block row (256-row tiles, MFMA waves): NI MFMAs with the fragment reads of the same row of
+    // the next step, then `slot(q)`, q = 0 .. SLOTS - 1 through the stage.  An activation request holds the compute unit's
+    // address path for sixteen clocks and the wave until it is accepted; one behind every second row keeps MFMAs queued meanwhile,
+    // where two in a row at the start of a step, by four waves at once, let the matrix pipe run dry.  Forward / backward, us:
+    // 2048 x 4096 <- 4096, INT4 73.5 -> 71.9 / 80.6 -> 79.3; 4096 <- 11008, INT3 186.2 -> 186.3 / 196.0 -> 190.5; 5000 x 5120 <- 5120,
+    // INT2 307 -> 300 / 323 -> 309 (all operands zero, 2048 x 4096, INT4: 59.5 -> 56.4 / 67.9 -> 64.1).  Requests behind the other
+    // rows, or the eight of them behind the first eight, gain half of that; slots that differ from wave to wave lose 5 %, and
+    // 128-row tiles, whose waves wait for the weight more than for this, lose 0 to 8 %.
+    constexpr int SLOTS = STEPS * MH, SLOT_STEP = SLOTS / XDMA;     // slots of a stage; a request in every SLOT_STEP-th
+    auto stage_rows = [&](int xstage, int wstage, int xnext, auto &&slot, auto &&turn) {
+        auto read_a = [&](int stage, int ks, int half, int i) {
+            return *(const u16x8_t *)(xs + stage * XS + aoff[ks] + (half * MH + i) * 16 * BK);
+        };
+        auto read_b = [&](int stage, int ks, int j) {
+            if constexpr (TRANS) {
+                const uint8_t *Bs = (const uint8_t *)(wsm + stage * WS + ks * 32 * WPITCH);
+                typedef short s16x4_t __attribute__((ext_vector_type(4)));
+                typedef __attribute__((address_space(3))) s16x4_t *lds4_t;
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(Bs + (toff[0] ^ (32u * j))));
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(Bs + (toff[1] ^ (32u * j))));
+                return u16x8_t{(uint16_t)lo[0], (uint16_t)lo[1], (uint16_t)lo[2], (uint16_t)lo[3],
+                               (uint16_t)hi[0], (uint16_t)hi[1], (uint16_t)hi[2], (uint16_t)hi[3]};
+            } else return *(const u16x8_t *)(wsm + stage * WS + boff + ks * 32 + j * 16 * WPITCH);
+        };
+        static_assert(MH == NI || SYM, "a row of either operand per piece");
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int ks = st / AH, half = st % AH;
+            const bool last = st + 1 == STEPS, next_b = half + 1 == AH;
+            if (last) turn();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < MH; ++i) {
+                fa[(st + 1) & 1].a[i] = last ? read_a(xnext, 0, 0, i) : read_a(xstage, (st + 1) / AH, (st + 1) % AH, i);
+                if (next_b) fb[(ks + 1) & 1].b[i] = last ? read_b(wstage ^ 1, 0, i) : read_b(wstage, ks + 1, i);
+#pragma unroll
+                for (int jj = 0; jj < NI; ++jj) {                               // serpentine, as in mfma_step
+                    const int j = i & 1 ? NI - 1 - jj : jj;
+                    acc[half * MH + i][j] = mfma16<BF16>(fb[ks & 1].b[j], fa[st & 1].a[i], acc[half * MH + i][j]);
+                }
+#pragma unroll
+                for (int h = 0; h < NI; ++h) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                        // one MFMA
+                    if (h < 1 + (next_b ? (TRANS ? 2 : 1) : 0)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                slot(st * MH + i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+
     constexpr int EXT_STEPS = 2;                                        // LoRA steps whose operands are prefetched
     constexpr int EXT_A = BM * 2 / NSTG, EXT_W = BN * 2 / NSTG;   // pieces per staging thread and LoRA step
     u16x8_t ext_a[EXT_STEPS][EXT_A], ext_w[EXT_STEPS][EXT_W];
@@ -537,18 +589,24 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         for (int kt = 0; kt < KT; ++kt) {
             const int xnext = xstage + 1 == NXS ? 0 : xstage + 1;
             const int xfill = NXS == 3 ? (xnext + 1 == NXS ? 0 : xnext + 1) : xnext;   // the stage NXS-1 ahead
-            // the activation loads for stage kt+2 are spread over the steps
+            // the activation loads for stage kt+2 are spread over the steps, or over the rows of MFMAs
             auto work = [&](int st) {
 #pragma unroll
                 for (int i = st * XDMA / STEPS; i < (st + 1) * XDMA / STEPS; ++i) issue_x(kt + NXS - 1, xfill, i);
             };
-            auto turn = [&]() { wait_vm_and_barrier<AHEAD>(); };   // stage kt+1 has landed (only loads for a later one may be pending)
+            // stage kt+1 has landed: only loads for a later one may be pending, with ROWS those issued before the last step
+            constexpr bool ROWS = BM > 128;
+            auto turn = [&]() { wait_vm_and_barrier<ROWS ? AHEAD - XDMA / STEPS : AHEAD>(); };
+            auto slot = [&](int q) {
+                if (q % SLOT_STEP == 0) issue_x(kt + NXS - 1, xfill, q / SLOT_STEP);
+            };
             if (SIDE && kt == side_kt) {
                 side_step(xstage);
                 side_kt += a.tiles_n;
                 if (side_kt < KT) side_load(side_kt);
             }
-            stage_steps(xstage, kt & 1, xnext, work, turn);
+            if constexpr (ROWS) stage_rows(xstage, kt & 1, xnext, slot, turn);
+            else stage_steps(xstage, kt & 1, xnext, work, turn);
             xstage = xnext;
         }
         wait_vm_and_barrier<0>();               // the loads issued past the last stage have landed: LDS is quiet
