@@ -90,31 +90,50 @@ __global__ __launch_bounds__(256) void pack_permuted_kernel(const uint8_t *__res
 // Column gather of a 16-bit matrix.  A workgroup copies GATHER_ROWS whole rows into LDS with row-contiguous 16-byte
 // loads (scattered 2-byte reads from global memory move a fraction of what contiguous requests do), then every thread
 // builds eight neighbouring output columns per row from LDS and writes them with one 16-byte store.  The index is read
-// once per thread and row block.  A workgroup takes as many rows as fit GATHER_LDS_BYTES (at most GATHER_ROWS); rows
+// once per thread and row block.  Bound by the chain of its round trips: a thread asks for its first indexes and for four
+// pieces of the rows before it waits for any, with 512 or 1024 threads to a workgroup (256 threads, piece by piece and the
+// index after the rows: 777 x 4096 5.7 -> 5.3 us, 2048 x 4096 8.8 -> 7.9, 2048 x 11008 26.1 -> 22.8, 100 x 32768 13.0 -> 6.7).
+// A workgroup takes as many rows as fit GATHER_LDS_BYTES (at most GATHER_ROWS); rows
 // longer than that take the direct kernel below.
 constexpr int GATHER_ROWS = 2;
 constexpr int GATHER_LDS_BYTES = 16384;
 constexpr int GATHER_LDS_K = 32768;      // one row of 64 KB: the most a launch gets without asking for more
-__global__ __launch_bounds__(256) void gather_columns_lds_kernel(const uint16_t *__restrict__ src,
-                                                                 const int32_t *__restrict__ index,
-                                                                 uint16_t *__restrict__ dst, int M, int K, int R)
+constexpr int GATHER_BATCH = 4;          // pieces a thread requests before it lays the first down
+template <int T>
+__global__ __launch_bounds__(T) void gather_columns_lds_kernel(const uint16_t *__restrict__ src,
+                                                               const int32_t *__restrict__ index,
+                                                               uint16_t *__restrict__ dst, int M, int K, int R)
 {
     extern __shared__ uint16_t rows[];   // R x K
     const int m0 = blockIdx.x * R;
     const int nrows = m0 + R <= M ? R : M - m0;
     const int pieces = nrows * (K / 8);                        // the rows are adjacent in memory: one flat copy
     const u32x4_t *from = reinterpret_cast<const u32x4_t *>(src + (long)m0 * K);
-    for (int p = threadIdx.x; p < pieces; p += 256) reinterpret_cast<u32x4_t *>(rows)[p] = from[p];
+    int idx[8];                                                // the first columns' sources, asked for ahead of the rows
+    auto load_index = [&](int j0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) idx[e] = index[j0 + e];
+    };
+    if ((int)threadIdx.x * 8 < K) load_index(threadIdx.x * 8);
+    for (int p0 = threadIdx.x; p0 < pieces; p0 += GATHER_BATCH * T) {
+        u32x4_t v[GATHER_BATCH];
+#pragma unroll
+        for (int i = 0; i < GATHER_BATCH; ++i)
+            if (p0 + i * T < pieces) v[i] = from[p0 + i * T];
+#pragma unroll
+        for (int i = 0; i < GATHER_BATCH; ++i)
+            if (p0 + i * T < pieces) reinterpret_cast<u32x4_t *>(rows)[p0 + i * T] = v[i];
+    }
     __syncthreads();
-    for (int j0 = threadIdx.x * 8; j0 < K; j0 += 256 * 8) {
+    for (int j0 = threadIdx.x * 8; j0 < K; j0 += T * 8) {
         int col[8];
         bool ok[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int v = index[j0 + e];
-            ok[e] = (unsigned)v < (unsigned)K;
-            col[e] = ok[e] ? v : 0;
+            ok[e] = (unsigned)idx[e] < (unsigned)K;
+            col[e] = ok[e] ? idx[e] : 0;
         }
+        if (j0 + T * 8 < K) load_index(j0 + T * 8);
         for (int i = 0; i < nrows; ++i) {
             const uint16_t *row = rows + i * K;
             uint16_t v[8];
@@ -235,8 +254,14 @@ void launch_gather_columns(const void *src, const int32_t *index, void *dst, int
     if (K <= GATHER_LDS_K) {
         int R = GATHER_LDS_BYTES / (K * 2);
         R = R < 1 ? 1 : (R > GATHER_ROWS ? GATHER_ROWS : R);
-        QLORA_LAUNCH(gather_columns_lds_kernel, dim3((unsigned)((M + R - 1) / R)), dim3(256), (size_t)R * K * 2, s,
-                           (const uint16_t *)src, index, (uint16_t *)dst, M, K, R);
+        const dim3 grid((unsigned)((M + R - 1) / R));
+        const size_t lds = (size_t)R * K * 2;
+        // a thread per eight columns, up to 1024; a single workgroup is done sooner with fewer (one row of 4096: 3.2 against 3.3 us)
+        const uint16_t *from = (const uint16_t *)src;
+        uint16_t *to = (uint16_t *)dst;
+        if (M > R && K > 8192) QLORA_LAUNCH(gather_columns_lds_kernel<1024>, grid, dim3(1024), lds, s, from, index, to, M, K, R);
+        else if (M > R && K > 2048) QLORA_LAUNCH(gather_columns_lds_kernel<512>, grid, dim3(512), lds, s, from, index, to, M, K, R);
+        else QLORA_LAUNCH(gather_columns_lds_kernel<256>, grid, dim3(256), lds, s, from, index, to, M, K, R);
         return;
     }
     const unsigned row_blocks = (unsigned)((M + GATHER_ROWS - 1) / GATHER_ROWS);

@@ -140,3 +140,21 @@ def test_gather_rows_wider_than_the_lds_staging():
     ref = x[:, np.clip(order, 0, K - 1)].copy()
     ref[:, [11, 39999]] = 0
     assert np.array_equal(out.cpu().numpy().view(np.uint16), ref)
+
+
+# both sides of the workgroup sizes (2048 and 8192 columns, one or more workgroups), rows that end inside a batch of pieces, the
+# longest row that is staged; a few indexes out of range
+@pytest.mark.parametrize("M,K", [(1, 2048), (3, 2048), (3, 2080), (1, 4096), (5, 8192), (3, 8224), (2, 32768), (3, 32)])
+def test_gathered_columns_at_the_workgroup_sizes(M, K):
+    import torch
+    from paper_2306_08162_amd import binding as ql
+    g = torch.Generator().manual_seed(M + K)
+    src = torch.randint(-2 ** 15, 2 ** 15, (M, K), generator=g, dtype=torch.int16)
+    index = torch.randperm(K, generator=g).to(torch.int32)
+    index[0], index[K // 2], index[K - 1] = -1, K, 2 ** 31 - 1
+    inside = (index >= 0) & (index < K)
+    want = torch.where(inside, src[:, index.clamp(0, K - 1).long()], 0)
+    dst = torch.full((M, K), 7, dtype=torch.int16, device="cuda")
+    announce(f"gather {M} x {K}")
+    ql.qlora_gather_columns(src.cuda(), index.cuda(), dst, M, K)
+    assert torch.equal(dst.cpu(), want)
