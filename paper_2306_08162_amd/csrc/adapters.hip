@@ -65,10 +65,9 @@ constexpr int ss_buf_bytes()      // operands of one stretch (+ 256 bytes for ke
     return (NATURAL ? SK_ROWS * 128 + SS_COLS * RG * 16 * 2 : (SK_ROWS + 16 * RG) * 128) + (MASKED ? 256 : 0);
 }
 template <bool BF16, int RG, int SK_ROWS, bool NATURAL, bool MASKED>
-__global__ __launch_bounds__(SK_WAVES * 64) void skinny_rows_staged_kernel(const uint16_t *__restrict__ act,
-                                                                          const uint16_t *__restrict__ small,
-                                                                          uint16_t *__restrict__ out, int M, int C, int r,
-                                                                          const uint8_t *__restrict__ keep, float keep_scale)
+__device__ __forceinline__ void skinny_rows_staged_body(const int block, const uint16_t *__restrict__ act,
+                                                        const uint16_t *__restrict__ small, uint16_t *__restrict__ out,
+                                                        int M, int C, int r, const uint8_t *__restrict__ keep, float keep_scale)
 {
     static_assert(!(NATURAL && MASKED), "the mask belongs to x, the activation operand of t = x A^T");
     extern __shared__ __attribute__((aligned(16))) char ss_lds[];   // [SK_WAVES][2] buffers; then the final sum
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(SK_WAVES * 64) void skinny_rows_staged_kernel(const
     constexpr int XDMA = SK_ROWS / 8;                // loads of token rows per stretch
     constexpr int SDMA_MAX = 2 * RG;                 // loads of `small` per stretch, at most (16 RG rows or 64 x 16 RG columns)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int m0 = blockIdx.x * SK_ROWS;
+    const int m0 = block * SK_ROWS;
     const int li = lane & 15, q = lane >> 4;
     const bool rowin = li < SK_ROWS;
     char *mine = ss_lds + wave * (2 * BUF);
@@ -199,6 +198,37 @@ __global__ __launch_bounds__(SK_WAVES * 64) void skinny_rows_staged_kernel(const
         if constexpr (MASKED) s *= keep_scale;
         if (row < SK_ROWS && m0 + row < M && g * 16 + col < r) out[(long)(m0 + row) * r + g * 16 + col] = to16<BF16>(s);
     }
+}
+
+template <bool BF16, int RG, int SK_ROWS, bool NATURAL, bool MASKED>
+__global__ __launch_bounds__(SK_WAVES * 64) void skinny_rows_staged_kernel(const uint16_t *__restrict__ act,
+                                                                          const uint16_t *__restrict__ small,
+                                                                          uint16_t *__restrict__ out, int M, int C, int r,
+                                                                          const uint8_t *__restrict__ keep, float keep_scale)
+{
+    skinny_rows_staged_body<BF16, RG, SK_ROWS, NATURAL, MASKED>((int)blockIdx.x, act, small, out, M, C, r, keep, keep_scale);
+}
+
+// u = dY B (the first half of the workgroups) and t = x A^T (the second): a backward pass that recomputes t needs both, and
+// either alone leaves most of the chip idle up to a few thousand tokens and is bound by its latency.  Backward pass without a
+// saved t, us: 4096 x 4096, 777 tokens, rank 8 58.8 -> 54.3 (masked 63.8 -> 58.8), 2048 tokens 82.8 -> 79.1, 300 tokens,
+// rank 32 45.2 -> 39.7; 5120 x 5120, 130 tokens, rank 64 56.9 -> 45.8.
+struct SkinnyPair {
+    const uint16_t *act[2], *small[2];
+    uint16_t *out[2];
+    int C[2], M, r;
+    const uint8_t *keep;      // keep bits of x, or NULL
+    float keep_scale;
+};
+template <bool BF16, int RG, int SK_ROWS, bool MASKED>
+__global__ __launch_bounds__(SK_WAVES * 64) void skinny_pair_kernel(const SkinnyPair a)
+{
+    const int half = (int)gridDim.x / 2, b = (int)blockIdx.x;
+    if (b < half)
+        skinny_rows_staged_body<BF16, RG, SK_ROWS, true, false>(b, a.act[0], a.small[0], a.out[0], a.M, a.C[0], a.r, nullptr, 1.f);
+    else
+        skinny_rows_staged_body<BF16, RG, SK_ROWS, false, MASKED>(b - half, a.act[1], a.small[1], a.out[1], a.M, a.C[1], a.r, a.keep,
+                                                                  a.keep_scale);
 }
 
 // Arguments of the adapter-gradient launch: dB (problem 0: act = dY, side = t) and dA (problem 1: act = x, side = u).
@@ -420,6 +450,28 @@ void launch_skinny_staged_rank(const uint16_t *act, const uint16_t *small, uint1
     }
 }
 
+template <bool BF16, int RG, int SK_ROWS, bool MASKED>
+void launch_skinny_pair(const SkinnyPair &a, hipStream_t s)
+{
+    constexpr int p0 = SK_WAVES * 2 * ss_buf_bytes<RG, SK_ROWS, true, false>(), p1 = SK_WAVES * 2 * ss_buf_bytes<RG, SK_ROWS, false, MASKED>();
+    constexpr int sum = SK_WAVES * RG * 16 * 17 * 4, pipe = p0 > p1 ? p0 : p1, lds = pipe > sum ? pipe : sum;
+    static_assert(lds <= 160 * 1024, "fits the LDS of a CU");
+    auto kern = skinny_pair_kernel<BF16, RG, SK_ROWS, MASKED>;
+    ensure_dynamic_lds((const void *)kern, (int)(lds));
+    QLORA_LAUNCH(kern, dim3(2 * ((a.M + SK_ROWS - 1) / SK_ROWS)), dim3(SK_WAVES * 64), lds, s, a);
+}
+
+template <bool BF16, bool MASKED>
+void launch_skinny_pair_rank(const SkinnyPair &a, hipStream_t s)
+{
+    switch ((a.r + 15) / 16) {
+    case 1: launch_skinny_pair<BF16, 1, 8, MASKED>(a, s); break;
+    case 2: launch_skinny_pair<BF16, 2, 8, MASKED>(a, s); break;
+    case 3: launch_skinny_pair<BF16, 3, 8, MASKED>(a, s); break;
+    default: launch_skinny_pair<BF16, 4, 8, MASKED>(a, s); break;
+    }
+}
+
 template <bool BF16, bool MASKED>
 void launch_skinny(const uint16_t *act, const uint16_t *small, uint16_t *out, int M, int C, int r, const uint8_t *keep,
                    float keep_scale, hipStream_t s)
@@ -548,6 +600,25 @@ void launch_lora_u(const void *dy, const void *B, void *u, int M, int N, int r, 
     } else {
         if (bf16) launch_skinny_staged_rank<true, 8, true, false>(a, b, o, M, N, r, nullptr, 1.f, s);
         else launch_skinny_staged_rank<false, 8, true, false>(a, b, o, M, N, r, nullptr, 1.f, s);
+    }
+}
+
+void launch_lora_u_and_down(const void *dy, const void *B, void *u, const void *x, const void *A, void *t, int M, int N, int K,
+                            int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s)
+{
+    if (M >= 16 * 256) {        // sixteen rows to a workgroup, and enough of them for either product
+        launch_lora_u(dy, B, u, M, N, r, bf16, s);
+        launch_lora_down(x, A, t, M, K, r, bf16, keep, keep_scale, s);
+        return;
+    }
+    const SkinnyPair a{{(const uint16_t *)dy, (const uint16_t *)x}, {(const uint16_t *)B, (const uint16_t *)A},
+                       {(uint16_t *)u, (uint16_t *)t}, {N, K}, M, r, (const uint8_t *)keep, keep_scale};
+    if (keep) {
+        if (bf16) launch_skinny_pair_rank<true, true>(a, s);
+        else launch_skinny_pair_rank<false, true>(a, s);
+    } else {
+        if (bf16) launch_skinny_pair_rank<true, false>(a, s);
+        else launch_skinny_pair_rank<false, false>(a, s);
     }
 }
 

@@ -487,7 +487,10 @@ static int backward(const void *dy, const void *x, const uint32_t *packed, const
     const bool side = !keep_mask && workspace_bytes >= w.total && gemm_side_floats(M, K, N, rank, false) > 0;
     if (rank > 0) {
         u = ws + w.u_off;
-        if (!side) launch_lora_u(dy, B, u, M, N, rank, p.bf16, s);
+        if (!side && !t_saved && !t_ready) {
+            launch_lora_u_and_down(dy, B, u, x, A, ws + w.t_off, M, N, K, rank, p.bf16, keep_mask, keep_scale, s);
+            t_ready = true;
+        } else if (!side) launch_lora_u(dy, B, u, M, N, rank, p.bf16, s);
     }
     mark_pre_end(s);
     {

@@ -61,6 +61,9 @@ void launch_lora_dx_masked(void *dx, const void *u, const void *A, const uint32_
                            bool bf16, hipStream_t s);
 // u[M,r] = dy[M,N] B[N,r]
 void launch_lora_u(const void *dy, const void *B, void *u, int M, int N, int r, bool bf16, hipStream_t s);
+// both (t as launch_lora_down without planes), one launch below 4096 token rows
+void launch_lora_u_and_down(const void *dy, const void *B, void *u, const void *x, const void *A, void *t, int M, int N, int K,
+                            int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s);
 // dB[N,r] = sc * dy[M,N]^T t[M,r] and dA[r,K] = sc * u[M,r]^T x[M,K], one launch for both, sums in a fixed order.
 // beta != 0: dB = beta*dB + ..., dA likewise.  keep != NULL (LoRA dropout): x stands for keep_scale * x * keep in dA.
 // Stacked adapters: t and u are [M, r_all], the first `frozen` adapter columns have no gradient, r = r_all - frozen,

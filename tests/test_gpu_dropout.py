@@ -92,3 +92,30 @@ def test_dropout_extremes():
     inp = small_inputs(5, 33, 256, 136, 4, 64, 8, "f16")
     _check(inp, 0.0)            # nothing dropped: the plain layer
     _check(inp, 0.999999)       # (almost surely) everything dropped: the adapter is gone
+
+
+# t and u from one launch (t not saved, contraction not split): every rank group, ragged token rows, N and K of different
+# lengths; the recomputed t has to give the bits that the saved one gives
+@pytest.mark.parametrize("masked", [False, True], ids=["plain", "masked"])
+@pytest.mark.parametrize("case", [(577, 96, 264, 8, "f16"), (130, 352, 64, 24, "bf16"), (41, 64, 1032, 40, "f16"),
+                                  (333, 480, 136, 64, "bf16")], ids=lambda c: "M{}_K{}_N{}_r{}_{}".format(*c))
+def test_recomputed_t_beside_u_gives_the_same_bits(case, masked):
+    import torch
+    from paper_2306_08162_amd.device import DeviceLayer
+    M, K, N, r, dtype = case
+    inp = small_inputs(M + K + N + r, M, K, N, 4, 32, r, dtype)
+    announce(f"recomputed t: {inp.cfg.name} masked={masked}")
+    layer = DeviceLayer(inp)
+    km = torch.from_numpy(_mask(5, M, K, 0.1)[1].view(np.int32)).to(layer.device)
+    got = []
+    for saved in (True, False):
+        if masked:
+            layer.forward_dropout(km, 1.0 / 0.9)
+            layer.backward_dropout(km, 1.0 / 0.9, use_saved_t=saved)
+        else:
+            layer.forward()
+            layer.backward(use_saved_t=saved)
+        torch.cuda.synchronize()
+        got.append([layer.host_dx().copy(), layer.host_dA().copy(), layer.host_dB().copy()])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
