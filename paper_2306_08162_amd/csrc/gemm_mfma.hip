@@ -980,15 +980,16 @@ void launch_tiles(GemmArgs &a, uint16_t *side_out, hipStream_t s)
     a.splits = 1;
     a.kt_split = (KC + BK - 1) / BK;
     // 128-row tiles while they are one round of the 256 CUs (a CU holds one workgroup), and if they are far fewer also the
-    // contraction split over several workgroups per tile.  A round of 128-row tiles takes 0.6 times as long as one of
-    // 256-row tiles (4096 x 4096, INT4, fp16: 39 and 64 us forward, 42 and 66 backward), so two rounds of them lose to one:
-    // M = 1397, 4096 x 4096, bf16 INT4 (352 tiles of 128 rows or 192 of 256) 79 -> 52 us forward, 76 -> 56 backward.
-    // Larger launches take 256-row tiles whatever the last round holds.  That is dear where it holds a few: 513 to 640 tokens
-    // to 11008 columns are 258 of them, and the backward pass takes 130 us where two rounds of 128-row tiles would take 92;
-    // but the ratio alone decides no better, for full rounds differ from it (3000 tokens, 4096 x 11008: 1.14 times as long
-    // by 0.6 * rounds).
+    // contraction split over several workgroups per tile.  A round of 128-row tiles takes 0.6 to 0.73 times as long as one of
+    // 256-row tiles (4096 x 4096, INT4, fp16: 39 and 64 us forward, 42 and 66 backward), so two rounds of them lose to one
+    // (M = 1397, 4096 x 4096, bf16 INT4, 352 tiles of 128 rows or 192 of 256: 79 and 52 us forward, 76 and 56 backward) and
+    // win against two, as in fp16 four do against three: 595 tokens to 11008 columns are 430 or 258 tiles, forward from 4096
+    // 99.8 -> 72.8 us, backward from 5120 121.8 -> 87.0; 1350 tokens 946 or 516, forward 162.7 -> 147.4 (bf16, whose 128-row tiles
+    // are slower, 0.94 to 1.03 times as long).  With more rounds the last one is too small a part of the launch (six against four,
+    // five and more: 1.04 to 1.4 times as long).
     if constexpr (BM == 256) {
-        if (((a.M + 127) / 128) * a.tiles_n <= 256) {
+        const int tall = (a.M + 255) / 256 * a.tiles_n, flat = (a.M + 127) / 128 * a.tiles_n;
+        if (flat <= 256 || (flat <= 512 && tall > 256) || (!BF16 && flat <= 1024 && tall > 512)) {
             a.tiles_m = (a.M + 127) / 128;
             if constexpr (TRANS) {
                 if (a.keep) {           // the masked epilogue needs the whole contraction in one workgroup
@@ -1028,12 +1029,20 @@ void launch_tiles(GemmArgs &a, uint16_t *side_out, hipStream_t s)
             return;
         }
     }
-    // At least one 256 x 256 tile per compute unit, and rounds of 256 tiles that are at least 80 % full: the
-    // symmetric-wave kernel (5-11 % less time than the 256 x 128 tiles at M = 4096 and 8192; a launch of 344 tiles,
-    // two rounds of which the second is a third full, is 10 % slower than the 688 smaller tiles).
+    // 256 x 256 tiles, by the symmetric-wave kernel, where they take at most half the rounds of the 256 x 128 tiles or fill
+    // theirs nearly (5-11 % less time at M = 4096 and 8192); a launch of 344 tiles, two rounds of which the second is a third
+    // full, is 10 % slower than the 688 smaller tiles in three, and 1026 tiles, five rounds, 6 % slower than 2052 in nine.
+    // One round of them, up to 4/5 full, beside two of the smaller tiles: fp16 forward 0.83 to 0.99 times as long (1110 tokens,
+    // 8192 <- 2048, INT3 55 -> 51 us), fp16 backward with 2 and 4 bits 0.93 to 0.98 (738 tokens, 13824 <- 11008: 260 -> 230 us);
+    // 0.95 to 1.04 where it is fuller, where the backward pass unpacks 3 or 8 bits, and in bf16.
     {
         const int tn = (NO + 255) / 256, tiles = a.tiles_m * tn, rounds = (tiles + 255) / 256;
-        if (tiles >= 256 && tiles * 10 >= rounds * 256 * 8) {
+        const int small_rounds = (a.tiles_m * a.tiles_n + 255) / 256;
+        const bool half = 2 * rounds <= small_rounds, full = tiles * 10 >= rounds * 256 * 8;
+        bool take;
+        if (tiles >= 256) take = half ? !BF16 || full : tiles * 20 >= rounds * 256 * 17;
+        else take = half && !full && !BF16 && (!TRANS || BITS == 2 || BITS == 4);
+        if (take) {
             a.tiles_n = tn;
             launch_variant<BITS, BF16, TRANS, 256, 256, 2, 4, false, true>(a, s);
             return;

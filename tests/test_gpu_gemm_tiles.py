@@ -20,6 +20,18 @@ def test_tile_height_boundary(case):
     check_layer(small_inputs(M + 3 * K + N + bits, M, K, N, bits, 32, 8, dtype))
 
 
+# launches of several rounds: two of 128-row tiles (430) instead of two of 256-row tiles (258), one of 256 x 256 tiles (129) instead
+# of the same two, four of 128-row tiles (946) instead of three (516); forward into many columns, then backward
+ROUNDS = [(577, 128, 11008, 4, "f16"), (577, 11008, 128, 2, "bf16"), (700, 128, 11008, 3, "f16"), (700, 11008, 128, 4, "f16"),
+          (1290, 128, 11008, 8, "f16"), (1290, 11008, 128, 3, "f16")]
+
+
+@pytest.mark.parametrize("case", ROUNDS, ids=lambda c: "M{}_K{}_N{}_b{}_{}".format(*c))
+def test_tile_shape_by_rounds(case):
+    M, K, N, bits, dtype = case
+    check_layer(small_inputs(M + K + N + bits, M, K, N, bits, 32, 8, dtype))
+
+
 # split contractions at ranks 8 and 16: fewer tile columns than stages of a split (33), a contraction that ends inside a stage
 # (2080, 1032), a last split shorter than the tile columns (4160), 8-bit codes at 28 tokens (tiled backward pass only)
 SIDE = [(33, 4096, 512, 4, 8, "f16"), (130, 2080, 1032, 3, 8, "bf16"), (40, 1024, 4160, 2, 16, "f16"),
