@@ -1034,7 +1034,8 @@ void launch_tiles(GemmArgs &a, uint16_t *side_out, hipStream_t s)
     // full, is 10 % slower than the 688 smaller tiles in three, and 1026 tiles, five rounds, 6 % slower than 2052 in nine.
     // One round of them, up to 4/5 full, beside two of the smaller tiles: fp16 forward 0.83 to 0.99 times as long (1110 tokens,
     // 8192 <- 2048, INT3 55 -> 51 us), fp16 backward with 2 and 4 bits 0.93 to 0.98 (738 tokens, 13824 <- 11008: 260 -> 230 us);
-    // 0.95 to 1.04 where it is fuller, where the backward pass unpacks 3 or 8 bits, and in bf16.
+    // 0.95 to 1.04 where it is fuller, where the backward pass unpacks 3 or 8 bits, and in bf16.  Contractions of 128 to 768: 105
+    // of 108 calls 0.75 to 0.99 times as long, three 1.01 to 1.04 (1740 tokens, 7216 <- 384, INT4, the most).
     {
         const int tn = (NO + 255) / 256, tiles = a.tiles_m * tn, rounds = (tiles + 255) / 256;
         const int small_rounds = (a.tiles_m * a.tiles_n + 255) / 256;
