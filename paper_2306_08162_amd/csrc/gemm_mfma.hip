@@ -561,14 +561,19 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                 } else sf[ks] = *(const u16x8_t *)(a.side_w + (long)fr * a.K + k);
             }
         };
-        auto side_step = [&](int xstage) {
+        auto side_step = [&](int xstage, int kt) {
 #pragma unroll
-            for (int ks = 0; ks < BK / 32; ++ks)
+            for (int ks = 0; ks < BK / 32; ++ks) {
+                // past the end lie copies of the row's last elements: zero beside the zeros of sf, or an infinity among
+                // them would make a NaN of the sum
+                const bool in = (kt_first + kt) * BK + 32 * ks + 8 * fq < KC;
 #pragma unroll
                 for (int i = 0; i < SIDE_I; ++i) {
-                    const u16x8_t x = *(const u16x8_t *)(xs + xstage * XS + aoff[ks] + (wn * SIDE_I + i) * 16 * BK);
+                    u16x8_t x = *(const u16x8_t *)(xs + xstage * XS + aoff[ks] + (wn * SIDE_I + i) * 16 * BK);
+                    if (!in) x = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
                     sacc[i] = mfma16<BF16>(sf[ks], x, sacc[i]);             // D[j = 4 fq + v][m = fr]
                 }
+            }
         };
         if (SIDE && side_kt < KT) side_load(side_kt);           // the oldest requests: they have landed with the first stage
 #pragma unroll
@@ -601,7 +606,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                 if (q % SLOT_STEP == 0) issue_x(kt + NXS - 1, xfill, q / SLOT_STEP);
             };
             if (SIDE && kt == side_kt) {
-                side_step(xstage);
+                side_step(xstage, kt);
                 side_kt += a.tiles_n;
                 if (side_kt < KT) side_load(side_kt);
             }

@@ -58,3 +58,30 @@ def test_adapter_products_beside_a_split_gemm(case):
     for name in ("host_y", "host_dx"):
         a, b = (np.asarray(oracle.widen(getattr(l, name)(), dtype), np.float64) for l in (full, less))
         assert rel_fro(a, b) <= unit_roundoff(dtype), name
+
+
+# an infinity among the last elements of a contraction that ends inside a stage: it reaches t (u) as an infinity of the other
+# factor's sign, and dB (dA) through it; the elements staged past the end must not make a NaN of it
+@pytest.mark.parametrize("case", [(40, 1056, 2056, 2, 8, "f16"), (130, 2080, 1032, 3, 8, "bf16"), (45, 1056, 1032, 4, 16, "f16")],
+                         ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(*c))
+def test_infinity_at_the_end_of_a_split_contraction(case):
+    import torch
+    import oracle
+    from paper_2306_08162_amd.device import DeviceLayer
+    M, K, N, bits, r, dtype = case
+    inp = small_inputs(M + K + N + bits, M, K, N, bits, 32, r, dtype)
+    announce(f"infinity at the end: {inp.cfg.name}")
+    inf, mx, kx, my, ny = 0x7c00 if dtype == "f16" else 0x7f80, 5, K - 3, 7, N - 2
+    inp.x[mx, kx], inp.dy[my, ny] = inf, inf
+    x, dy, A, B = (oracle.widen(v, dtype) for v in (inp.x, inp.dy, inp.A, inp.B))
+    layer = DeviceLayer(inp)
+    layer.forward()
+    layer.backward()
+    torch.cuda.synchronize()
+    t = oracle.widen(layer.host_t(), dtype)
+    finite = np.arange(M) != mx
+    assert np.isfinite(t[finite]).all()
+    assert np.array_equal(t[mx], np.sign(A[:, kx]) * np.inf)
+    k, n = np.arange(K) != kx, np.arange(N) != ny
+    assert np.array_equal(layer.host_dA()[:, k], np.outer(np.sign(B[ny]), np.sign(x[my, k])) * np.inf)
+    assert np.array_equal(layer.host_dB()[n], np.outer(np.sign(dy[mx, n]), np.sign(A[:, kx])) * np.inf)
