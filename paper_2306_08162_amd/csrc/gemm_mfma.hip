@@ -561,21 +561,30 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                 } else sf[ks] = *(const u16x8_t *)(a.side_w + (long)fr * a.K + k);
             }
         };
-        auto side_step = [&](int xstage, int kt) {
+        auto side_step = [&](int xstage, auto &&inside) {
 #pragma unroll
-            for (int ks = 0; ks < BK / 32; ++ks) {
-                // past the end lie copies of the row's last elements: zero beside the zeros of sf, or an infinity among
-                // them would make a NaN of the sum
-                const bool in = (kt_first + kt) * BK + 32 * ks + 8 * fq < KC;
+            for (int ks = 0; ks < BK / 32; ++ks)
 #pragma unroll
                 for (int i = 0; i < SIDE_I; ++i) {
                     u16x8_t x = *(const u16x8_t *)(xs + xstage * XS + aoff[ks] + (wn * SIDE_I + i) * 16 * BK);
-                    if (!in) x = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
+                    if (!inside(ks)) x = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
                     sacc[i] = mfma16<BF16>(sf[ks], x, sacc[i]);             // D[j = 4 fq + v][m = fr]
                 }
+        };
+        // A contraction that ends inside a stage: past its end lie copies of the row's last elements, which have to be zero
+        // beside the zeros of sf, or an infinity among them would make a NaN of the sum.  Zeroing them in every stage costs 2 to
+        // 5 % where a workgroup takes most of its stages (642 x 64 <- 28672), so that last stage is taken after the loop.
+        [[maybe_unused]] const int side_tail = SIDE && KC % BK != 0 && kt_first + KT == (KC + BK - 1) / BK ? KT - 1 : KT;
+        [[maybe_unused]] bool at_tail = false;
+        auto side_fetch = [&]() {               // for the next stage, side_kt
+            if (side_kt >= KT) return;
+            side_load(side_kt);
+            if (side_kt == side_tail) {
+                at_tail = true;
+                side_kt = KT;
             }
         };
-        if (SIDE && side_kt < KT) side_load(side_kt);           // the oldest requests: they have landed with the first stage
+        if constexpr (SIDE) side_fetch();       // the oldest requests: they have landed with the first stage
 #pragma unroll
         for (int i = 0; i < XDMA; ++i) issue_x(0, 0, i);
         if constexpr (NXS == 3) {
@@ -606,15 +615,20 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
                 if (q % SLOT_STEP == 0) issue_x(kt + NXS - 1, xfill, q / SLOT_STEP);
             };
             if (SIDE && kt == side_kt) {
-                side_step(xstage, kt);
+                side_step(xstage, [](int) { return true; });
                 side_kt += a.tiles_n;
-                if (side_kt < KT) side_load(side_kt);
+                side_fetch();
             }
             if constexpr (ROWS) stage_rows(xstage, kt & 1, xnext, slot, turn);
             else stage_steps(xstage, kt & 1, xnext, work, turn);
             xstage = xnext;
         }
         wait_vm_and_barrier<0>();               // the loads issued past the last stage have landed: LDS is quiet
+        if constexpr (SIDE) {
+            if (at_tail)
+                side_step(xstage == 0 ? NXS - 1 : xstage - 1,
+                          [&](int ks) { return (kt_first + KT - 1) * BK + 32 * ks + 8 * fq < KC; });
+        }
     } else {
         // ---- weight staging waves ----
         // The operands of the LoRA steps that follow the main loop (up to two steps, ranks up to 32) are requested
