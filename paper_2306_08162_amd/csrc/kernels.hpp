@@ -88,14 +88,20 @@ inline int gemm_splits(int M, int NO, int KC)
 }
 // Floats of the partial sums of t (forward) or u (backward) that a split launch of rank r forms beside the GEMM: up to
 // min(tile columns, stages of a split) per split and token row.  0: t or u comes from a launch of its own.  That is so for
-// higher ranks, whose partial sums and adapter rows cost the kernel that adds them more than the launch saved (64 x 5120 <- 13824,
-// rank 32, forward 40.3 -> 44.1 us; 257 x 2080 <- 4104, backward 31.3 -> 32.1), and for rank 16 forward, where a thread's four
-// rows of B are 128 bytes (512 x 4096 <- 4096: 36.6 -> 38.4, 256: 30.6 -> 29.5).
+// - higher ranks, whose partial sums and adapter rows cost the kernel that adds them more than the launch saved (64 x 5120 <- 13824,
+//   rank 32, forward 40.3 -> 44.1 us; 257 x 2080 <- 4104, backward 31.3 -> 32.1), and rank 16 forward, where a thread's four
+//   rows of B are 128 bytes (512 x 4096 <- 4096: 36.6 -> 38.4, 256: 30.6 -> 29.5);
+// - backward, outputs of one tile column (its workgroups form u in all of their stages, from B's rows two bytes a lane) and
+//   more than twice as many token rows as columns (the kernel that adds the planes takes two rows to a workgroup, whatever
+//   their length): 427 x 128 <- 32000 72 us, 91 with u beside it; 3941 x 384 <- 5120 54 and 57.  Over 4700 shapes of ranks 8 and 16
+//   the whole backward pass takes 0.87 times as long with u beside the GEMM inside these bounds, 1.00 times outside;
+// - forward, 4096 token rows and more, where the launch of its own fills the chip: 10913 x 128 <- 1024 1.14 times as long.
 inline size_t gemm_side_floats(int M, int NO, int KC, int r, bool forward)
 {
     const int s = gemm_splits(M, NO, KC);
     if (s < 2 || !(r == 8 || (r == 16 && !forward))) return 0;
     const int tiles_n = (NO + GEMM_SPLIT_BN - 1) / GEMM_SPLIT_BN, kt = ((KC + 63) / 64 + s - 1) / s;
+    if (forward ? M >= 4096 : (tiles_n < 2 || M > 2 * GEMM_SPLIT_BN * tiles_n)) return 0;
     return (size_t)s * (tiles_n < kt ? tiles_n : kt) * M * r;
 }
 // part: gemm_splits(M, NO, KC) * M * NO floats when that count exceeds 1 (NO = N, KC = K forward; NO = K, KC = N
