@@ -88,7 +88,9 @@ size_t qlora_packed_words(int N, int K, int bits);
  * contraction is split over several workgroups, and beside those the partial
  * sums of t or u at ranks 8 and 16 (all summed in a fixed order, so results are
  * bitwise reproducible run to run).  A buffer that lacks the room for these last
- * ones only is accepted too; t and u then come from launches of their own.
+ * ones only is accepted too; t and u then come from launches of their own: t with
+ * the same bits, y and (through u) dx and dA with sums in another order, which may
+ * round an element the other way.
  */
 size_t qlora_workspace_bytes(int M, int N, int K, int bits, int group_size, int rank);
 
@@ -186,8 +188,10 @@ int qlora_linear_fwd_static(const void *x, const uint32_t *packed, const void *s
  * Backward pass (Fig. 1, backward path; Sec. 3.1).  Writes dx [M,K] in `dtype`,
  * and, when rank > 0, dA [r,K] and dB [N,r] in fp32 (overwritten, not
  * accumulated).  t_saved is the t_save of the matching forward call, or NULL to
- * have t recomputed from x and A (what gradient checkpointing does).  x is
- * needed for dA (and for recomputing t); with rank == 0 it may be NULL.
+ * have t recomputed from x and A (what gradient checkpointing does): above 32
+ * token rows the recomputed t has the bits of the saved one; up to 32 its sums
+ * may be in another order and an element, and dB through it, round the other
+ * way.  x is needed for dA (and for recomputing t); with rank == 0 it may be NULL.
  */
 int qlora_linear_bwd(const void *dy, const void *x, const uint32_t *packed, const void *scales,
                      const uint8_t *zeros, const void *A, const void *B, const void *t_saved,
@@ -214,7 +218,8 @@ int qlora_linear_bwd_accumulate(const void *dy, const void *x, const uint32_t *p
  *     dX = dY deq(W_q) + ((alpha/r) (dY B) A) * keep * keep_scale,   dA = (alpha/r) (dY B)^T x~,  dB unchanged in form
  * keep_mask: uint32 [M, K/32], drawn by the caller; element (m,k) is kept where bit k % 32 of word [m, k/32] is set.
  * The same mask goes to the forward and to the backward call; t_save / t_saved then hold t = x~ A^T.  keep_mask ==
- * NULL is no dropout: the calls are then qlora_linear_fwd and qlora_linear_bwd_accumulate.
+ * NULL is no dropout: the calls are then qlora_linear_fwd and qlora_linear_bwd_accumulate.  (A mask that keeps all with
+ * keep_scale 1 gives the same sums, not always in the same order.)
  */
 int qlora_linear_fwd_dropout(const void *x, const uint32_t *packed, const void *scales, const uint8_t *zeros,
                              const void *A, const void *B, const uint32_t *keep_mask, float keep_scale,

@@ -209,6 +209,134 @@ __global__ __launch_bounds__(SK_WAVES * 64) void skinny_rows_staged_kernel(const
     skinny_rows_staged_body<BF16, RG, SK_ROWS, NATURAL, MASKED>((int)blockIdx.x, act, small, out, M, C, r, keep, keep_scale);
 }
 
+// t = x A^T at rank 8 in the order in which a forward GEMM that splits its contraction sums it beside its tiles (see
+// gemm_side()), so that t has the same bits whichever of the two forms it: partial sum p is the MFMA chain over every
+// tiles_n-th stretch of its split, and the partial sums are added as the kernel that adds the planes does it.  Bound by latency: a
+// workgroup takes eight token rows, its wave w the partial sums w, w + 8, ... (from OR_BUFS stretches requested together), and
+// they meet in LDS.  Backward pass that recomputes t, us, with the kernel above and with this one: 247 x 4096 <- 4096, INT4 32.8
+// and 33.6; 242 x 4096 <- 11008, INT2 50.1 and 51.6; 285, INT4 62.1 and 62.6 (two stretches in flight, eight more rows of zeros and
+// the places found by division: 3 to 10 % more).
+constexpr int OR_BUFS = 4, OR_STRETCH = 2 * 8 * 128;       // stretches of a wave in flight; bytes of one: eight rows of x and of A
+constexpr int OR_PITCH = 8 * 8 + 8;                        // floats per partial sum: eight of them read at once hit all banks
+constexpr int ordered_lds(int parts) { return SK_WAVES * OR_BUFS * OR_STRETCH + parts * OR_PITCH * 4; }
+template <bool BF16>
+__device__ __forceinline__ void skinny_rows_ordered_body(const int block, const uint16_t *__restrict__ x, const uint16_t *__restrict__ A,
+                                                         uint16_t *__restrict__ t, int M, int K, const GemmSide &o)
+{
+    extern __shared__ __attribute__((aligned(16))) char ss_lds[];   // [SK_WAVES][OR_BUFS] stretches; then the partial sums
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m0 = block * 8, q = lane >> 4, row = lane & 7;        // the MFMA block's upper eight rows repeat the lower ones
+    const char *mine = ss_lds + wave * (OR_BUFS * OR_STRETCH);
+    const uint32_t mine_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)mine;
+    float *const part = reinterpret_cast<float *>(ss_lds + SK_WAVES * OR_BUFS * OR_STRETCH);
+
+    // loads as in skinny_rows_staged_body: row lane / 8, slot lane % 8 receives piece slot ^ row of the stretch
+    const int d_row = lane >> 3, d_piece = (lane & 7) ^ d_row;
+    const uint32_t xoff = (uint32_t)min(m0 + d_row, M - 1) * (uint32_t)K * 2u, aoff = (uint32_t)d_row * (uint32_t)K * 2u;
+    auto fetch = [&](int kt, int buf) {
+        const uint32_t cb = (uint32_t)min(kt * SS_COLS + 8 * d_piece, K - 8) * 2u;       // past the end: the last piece again
+        const uint32_t base = mine_lds + buf * OR_STRETCH;
+        dma16(x, xoff + cb, (uint32_t)__builtin_amdgcn_readfirstlane((int)base));
+        dma16(A, aoff + cb, (uint32_t)__builtin_amdgcn_readfirstlane((int)(base + 1024)));
+    };
+    float4_t acc = {0.f, 0.f, 0.f, 0.f};
+    auto consume = [&](int kt, int buf) {
+        const char *bp = mine + buf * OR_STRETCH + row * 128;
+        u16x8_t xf[2], af[2];
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+            xf[cc] = *(const u16x8_t *)(bp + ((4 * cc + q) ^ row) * 16);
+            af[cc] = *(const u16x8_t *)(bp + 1024 + ((4 * cc + q) ^ row) * 16);
+        }
+        if ((kt + 1) * SS_COLS > K) {
+#pragma unroll
+            for (int cc = 0; cc < 2; ++cc)
+                if (kt * SS_COLS + 32 * cc + 8 * q >= K) xf[cc] = af[cc] = u16x8_t{0, 0, 0, 0, 0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) acc = mfma16<BF16>(af[cc], xf[cc], acc);             // D[j = 4q + v][m = lane % 16]
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the buffer is read out before it is refilled
+    };
+
+    // the wave's stretches in order; p >= o.parts: there are no more
+    const int stretches = (K + SS_COLS - 1) / SS_COLS;
+    int p = wave, in_split = wave, first = 0, kt = 0, end = 0;      // partial sum, its number in the split, the split's stretches
+    auto enter = [&]() {
+        while (in_split >= o.per_split) {
+            in_split -= o.per_split;
+            first += o.kt_split;
+        }
+        kt = first + in_split;
+        end = min(first + o.kt_split, stretches);
+    };
+    auto settle = [&]() {                                           // on to a partial sum that has a stretch left
+        while (kt >= end && p < o.parts) {
+            p += SK_WAVES;
+            in_split += SK_WAVES;
+            enter();
+        }
+    };
+    int kts[OR_BUFS], ps[OR_BUFS];                                  // the stretches in flight, oldest first
+    enter();
+    settle();
+#pragma unroll
+    for (int i = 0; i < OR_BUFS; ++i) {
+        kts[i] = kt;
+        ps[i] = p;
+        if (p < o.parts) {
+            fetch(kt, i);
+            kt += o.tiles_n;
+            settle();
+        }
+    }
+    for (int e = wave; e < o.parts; e += SK_WAVES) part[e * OR_PITCH + lane] = 0.f;        // a partial sum may be empty
+    for (int buf = 0; ps[0] < o.parts; buf = (buf + 1) % OR_BUFS) {
+        static_assert(OR_BUFS == 4, "two loads for each younger stretch may be in flight");
+        if (ps[3] < o.parts) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        else if (ps[2] < o.parts) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else if (ps[1] < o.parts) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        consume(kts[0], buf);
+        if (ps[1] != ps[0]) {
+            if ((lane & 15) < 8 && q < 2) *(float4_t *)(part + ps[0] * OR_PITCH + row * 8 + 4 * q) = acc;
+            acc = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < OR_BUFS; ++i) {
+            kts[i] = kts[i + 1];
+            ps[i] = ps[i + 1];
+        }
+        kts[OR_BUFS - 1] = kt;
+        ps[OR_BUFS - 1] = p;
+        if (p < o.parts) {
+            fetch(kt, buf);
+            kt += o.tiles_n;
+            settle();
+        }
+    }
+    __syncthreads();
+    // token row `wave`: the sums of four waves of eight lane groups each, as the kernel that adds the planes forms them
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int e0 = 0; e0 < o.parts; e0 += 32)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const int e = e0 + 8 * w + (lane >> 3);
+            if (e < o.parts) v[w] += part[e * OR_PITCH + wave * 8 + row];
+        }
+#pragma unroll
+    for (int d = 8; d < 64; d <<= 1)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v[w] += __shfl_xor(v[w], d, 64);
+    if (lane < 8 && m0 + wave < M) t[(long)(m0 + wave) * 8 + lane] = to16<BF16>(v[0] + v[1] + v[2] + v[3]);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(SK_WAVES * 64) void skinny_rows_ordered_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ A,
+                                                                           uint16_t *__restrict__ t, int M, int K, const GemmSide o)
+{
+    skinny_rows_ordered_body<BF16>((int)blockIdx.x, x, A, t, M, K, o);
+}
+
 // u = dY B (the first half of the workgroups) and t = x A^T (the second): a backward pass that recomputes t needs both, and
 // either alone leaves most of the chip idle up to a few thousand tokens and is bound by its latency.  Backward pass without a
 // saved t, us: 4096 x 4096, 777 tokens, rank 8 58.8 -> 54.3 (masked 63.8 -> 58.8), 2048 tokens 82.8 -> 79.1, 300 tokens,
@@ -219,13 +347,16 @@ struct SkinnyPair {
     int C[2], M, r;
     const uint8_t *keep;      // keep bits of x, or NULL
     float keep_scale;
+    GemmSide order;           // of t
 };
-template <bool BF16, int RG, int SK_ROWS, bool MASKED>
+template <bool BF16, int RG, int SK_ROWS, bool MASKED, bool ORDERED>
 __global__ __launch_bounds__(SK_WAVES * 64) void skinny_pair_kernel(const SkinnyPair a)
 {
     const int half = (int)gridDim.x / 2, b = (int)blockIdx.x;
     if (b < half)
         skinny_rows_staged_body<BF16, RG, SK_ROWS, true, false>(b, a.act[0], a.small[0], a.out[0], a.M, a.C[0], a.r, nullptr, 1.f);
+    else if constexpr (ORDERED)
+        skinny_rows_ordered_body<BF16>(b - half, a.act[1], a.small[1], a.out[1], a.M, a.C[1], a.order);
     else
         skinny_rows_staged_body<BF16, RG, SK_ROWS, false, MASKED>(b - half, a.act[1], a.small[1], a.out[1], a.M, a.C[1], a.r, a.keep,
                                                                   a.keep_scale);
@@ -450,20 +581,36 @@ void launch_skinny_staged_rank(const uint16_t *act, const uint16_t *small, uint1
     }
 }
 
-template <bool BF16, int RG, int SK_ROWS, bool MASKED>
+template <bool BF16>
+void launch_skinny_ordered(const uint16_t *x, const uint16_t *A, uint16_t *t, int M, int K, const GemmSide &o, hipStream_t s)
+{
+    static_assert(ordered_lds(GEMM_SIDE_MAX_PARTS) <= 160 * 1024, "fits the LDS of a CU");
+    auto kern = skinny_rows_ordered_kernel<BF16>;
+    ensure_dynamic_lds((const void *)kern, ordered_lds(GEMM_SIDE_MAX_PARTS));
+    QLORA_LAUNCH(kern, dim3((M + 7) / 8), dim3(SK_WAVES * 64), ordered_lds(o.parts), s, x, A, t, M, K, o);
+}
+
+template <bool BF16, int RG, int SK_ROWS, bool MASKED, bool ORDERED = false>
 void launch_skinny_pair(const SkinnyPair &a, hipStream_t s)
 {
     constexpr int p0 = SK_WAVES * 2 * ss_buf_bytes<RG, SK_ROWS, true, false>(), p1 = SK_WAVES * 2 * ss_buf_bytes<RG, SK_ROWS, false, MASKED>();
-    constexpr int sum = SK_WAVES * RG * 16 * 17 * 4, pipe = p0 > p1 ? p0 : p1, lds = pipe > sum ? pipe : sum;
-    static_assert(lds <= 160 * 1024, "fits the LDS of a CU");
-    auto kern = skinny_pair_kernel<BF16, RG, SK_ROWS, MASKED>;
-    ensure_dynamic_lds((const void *)kern, (int)(lds));
+    constexpr int sum = SK_WAVES * RG * 16 * 17 * 4, pipe = p0 > p1 ? p0 : p1, plain = pipe > sum ? pipe : sum;
+    const int ordered = ORDERED ? ordered_lds(a.order.parts) : 0, lds = ordered > plain ? ordered : plain;
+    static_assert(plain <= 160 * 1024, "fits the LDS of a CU");
+    auto kern = skinny_pair_kernel<BF16, RG, SK_ROWS, MASKED, ORDERED>;
+    ensure_dynamic_lds((const void *)kern, ORDERED ? ordered_lds(GEMM_SIDE_MAX_PARTS) : plain);
     QLORA_LAUNCH(kern, dim3(2 * ((a.M + SK_ROWS - 1) / SK_ROWS)), dim3(SK_WAVES * 64), lds, s, a);
 }
 
 template <bool BF16, bool MASKED>
 void launch_skinny_pair_rank(const SkinnyPair &a, hipStream_t s)
 {
+    if constexpr (!MASKED) {
+        if (a.order.parts > 0) {            // rank 8
+            launch_skinny_pair<BF16, 1, 8, false, true>(a, s);
+            return;
+        }
+    }
     switch ((a.r + 15) / 16) {
     case 1: launch_skinny_pair<BF16, 1, 8, MASKED>(a, s); break;
     case 2: launch_skinny_pair<BF16, 2, 8, MASKED>(a, s); break;
@@ -563,7 +710,7 @@ int lora_down_small_chunk(int K)
 int lora_down_small_planes(int K) { return (K + lora_down_small_chunk(K) - 1) / lora_down_small_chunk(K); }
 
 void launch_lora_down(const void *x, const void *A, void *t, int M, int K, int r, bool bf16, const uint32_t *keep,
-                      float keep_scale, hipStream_t s, float *planes)
+                      float keep_scale, hipStream_t s, float *planes, const GemmSide &order)
 {
     const uint16_t *xp = (const uint16_t *)x, *Ap = (const uint16_t *)A;
     uint16_t *tp = (uint16_t *)t;
@@ -578,6 +725,11 @@ void launch_lora_down(const void *x, const void *A, void *t, int M, int K, int r
             QLORA_LAUNCH(lora_down_small_partial_kernel<false>, dim3(np), dim3(256), 0, s, xp, Ap, planes, M, K, r, chunk);
             QLORA_LAUNCH(lora_down_small_sum_kernel<false>, sum_grid, dim3(256), 0, s, planes, tp, np, M * r);
         }
+        return;
+    }
+    if (order.parts > 0) {
+        if (bf16) launch_skinny_ordered<true>(xp, Ap, tp, M, K, order, s);
+        else launch_skinny_ordered<false>(xp, Ap, tp, M, K, order, s);
         return;
     }
     if (keep) {
@@ -604,15 +756,15 @@ void launch_lora_u(const void *dy, const void *B, void *u, int M, int N, int r, 
 }
 
 void launch_lora_u_and_down(const void *dy, const void *B, void *u, const void *x, const void *A, void *t, int M, int N, int K,
-                            int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s)
+                            int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s, const GemmSide &order)
 {
     if (M >= 16 * 256) {        // sixteen rows to a workgroup, and enough of them for either product
         launch_lora_u(dy, B, u, M, N, r, bf16, s);
-        launch_lora_down(x, A, t, M, K, r, bf16, keep, keep_scale, s);
+        launch_lora_down(x, A, t, M, K, r, bf16, keep, keep_scale, s, nullptr, order);
         return;
     }
     const SkinnyPair a{{(const uint16_t *)dy, (const uint16_t *)x}, {(const uint16_t *)B, (const uint16_t *)A},
-                       {(uint16_t *)u, (uint16_t *)t}, {N, K}, M, r, (const uint8_t *)keep, keep_scale};
+                       {(uint16_t *)u, (uint16_t *)t}, {N, K}, M, r, (const uint8_t *)keep, keep_scale, order};
     if (keep) {
         if (bf16) launch_skinny_pair_rank<true, true>(a, s);
         else launch_skinny_pair_rank<false, true>(a, s);

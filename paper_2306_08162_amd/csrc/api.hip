@@ -286,6 +286,13 @@ int qlora_linear_fwd(const void *x, const uint32_t *packed, const void *scales, 
                                     rank, alpha, dtype, workspace, workspace_bytes, stream);
 }
 
+// How the tiled forward pass sums t beside its GEMM, if it does: every launch that forms the t of such a call by itself
+// takes the same order, so that a recomputed t, and the t of a buffer without the room, has the bits of a saved one.
+static GemmSide t_order(int M, int N, int K, int rank, const uint32_t *keep_mask)
+{
+    return M > SMALL_M_FWD_MAX && !keep_mask ? gemm_side(M, N, K, rank, true) : GemmSide{};
+}
+
 // The forward pass behind every single-projection entry point.  `ws` + w.t_off holds t when it is not saved, `ws` +
 // w.split_off the planes of a split contraction; ws_bytes is what the caller's buffer holds beyond `ws`.
 // zpacked: the zero-points in their bit-packed storage form instead of `zeros`; a kernel that reads that form takes
@@ -326,10 +333,11 @@ static int forward(const void *x, const uint32_t *packed, const void *scales, co
         mark_pre_begin(s);
         if (zpacked) launch_unpack_zeros(zpacked, zscratch, N, K / group_size, bits, s);
         // a GEMM whose contraction is split forms t itself, for the kernel that sums its planes
-        const bool side = !keep_mask && ws_bytes >= w.total && gemm_side_floats(M, N, K, rank, true) > 0;
+        const GemmSide order = t_order(M, N, K, rank, keep_mask);
+        const bool side = order.parts > 0 && ws_bytes >= w.total;
         if (rank > 0 && !side) {
             t = t_save ? t_save : (void *)(ws + w.t_off);
-            launch_lora_down(x, A, t, M, K, rank, p.bf16, keep_mask, keep_scale, s);
+            launch_lora_down(x, A, t, M, K, rank, p.bf16, keep_mask, keep_scale, s, nullptr, order);
         }
         mark_pre_end(s);
         GemmTimer timer(s, true);
@@ -485,10 +493,11 @@ static int backward(const void *dy, const void *x, const uint32_t *packed, const
     if (zpacked && !unpacked) launch_unpack_zeros(zpacked, zscratch, N, K / group_size, bits, s);
     // as in forward(): a GEMM whose contraction is split forms u itself
     const bool side = !keep_mask && workspace_bytes >= w.total && gemm_side_floats(M, K, N, rank, false) > 0;
+    const GemmSide order = t_order(M, N, K, rank, keep_mask);
     if (rank > 0) {
         u = ws + w.u_off;
         if (!side && !t_saved && !t_ready) {
-            launch_lora_u_and_down(dy, B, u, x, A, ws + w.t_off, M, N, K, rank, p.bf16, keep_mask, keep_scale, s);
+            launch_lora_u_and_down(dy, B, u, x, A, ws + w.t_off, M, N, K, rank, p.bf16, keep_mask, keep_scale, s, order);
             t_ready = true;
         } else if (!side) launch_lora_u(dy, B, u, M, N, rank, p.bf16, s);
     }
@@ -512,7 +521,8 @@ static int backward(const void *dy, const void *x, const uint32_t *packed, const
     if (rank > 0) {
         const void *t = t_saved;
         if (!t) {
-            if (!t_ready) launch_lora_down(x, A, ws + w.t_off, M, K, rank, p.bf16, keep_mask, keep_scale, s);
+            if (!t_ready)
+                launch_lora_down(x, A, ws + w.t_off, M, K, rank, p.bf16, keep_mask, keep_scale, s, nullptr, order);
             t = ws + w.t_off;
         }
         launch_adapter_grads(dy, t, x, u, dB, dA, M, N, K, rank, frozen, p.sc, beta, keep_mask, keep_scale, p.bf16, s);

@@ -52,10 +52,16 @@ void launch_mfma_probe(float *out, int iters, bool random, hipStream_t s);
 // the row) t = keep_scale * (x * keep) A^T
 // planes != NULL, no mask and at most LORA_DOWN_SMALL_MAX_M token rows: the contraction is split over workgroups
 // (planes holds lora_down_small_planes(K) * M * r floats), two launches.
+// order.parts > 0 (rank 8, no mask): the sums in the order of the GEMM launch `order` describes, bit for bit
 constexpr int LORA_DOWN_SMALL_MAX_M = 32;
 int lora_down_small_planes(int K);
+struct GemmSide {       // partial sums of t or u that a split GEMM forms beside its tiles, see gemm_side()
+    int parts = 0;      // of a token row: splits x per_split; 0: none
+    int per_split = 1, kt_split = 0, tiles_n = 1;    // partial p of a split: its stages p, p + tiles_n, ... of kt_split
+};
+constexpr int GEMM_SIDE_MAX_PARTS = 256;
 void launch_lora_down(const void *x, const void *A, void *t, int M, int K, int r, bool bf16, const uint32_t *keep,
-                      float keep_scale, hipStream_t s, float *planes = nullptr);
+                      float keep_scale, hipStream_t s, float *planes = nullptr, const GemmSide &order = {});
 // dx[m,k] += f * keep[m,k] * sum_j u[m,j] A[j,k]: the adapter's share of dX under dropout, on top of the base product
 void launch_lora_dx_masked(void *dx, const void *u, const void *A, const uint32_t *keep, int M, int K, int r, float f,
                            bool bf16, hipStream_t s);
@@ -63,7 +69,7 @@ void launch_lora_dx_masked(void *dx, const void *u, const void *A, const uint32_
 void launch_lora_u(const void *dy, const void *B, void *u, int M, int N, int r, bool bf16, hipStream_t s);
 // both (t as launch_lora_down without planes), one launch below 4096 token rows
 void launch_lora_u_and_down(const void *dy, const void *B, void *u, const void *x, const void *A, void *t, int M, int N, int K,
-                            int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s);
+                            int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s, const GemmSide &order);
 // dB[N,r] = sc * dy[M,N]^T t[M,r] and dA[r,K] = sc * u[M,r]^T x[M,K], one launch for both, sums in a fixed order.
 // beta != 0: dB = beta*dB + ..., dA likewise.  keep != NULL (LoRA dropout): x stands for keep_scale * x * keep in dA.
 // Stacked adapters: t and u are [M, r_all], the first `frozen` adapter columns have no gradient, r = r_all - frozen,
@@ -86,8 +92,8 @@ inline int gemm_splits(int M, int NO, int KC)
     const int s = by_cus < by_depth ? by_cus : by_depth;
     return s > 8 ? 8 : (s < 1 ? 1 : s);
 }
-// Floats of the partial sums of t (forward) or u (backward) that a split launch of rank r forms beside the GEMM: up to
-// min(tile columns, stages of a split) per split and token row.  0: t or u comes from a launch of its own.  That is so for
+// The partial sums of t (forward) or u (backward) that a split launch of rank r forms beside the GEMM: min(tile columns, stages
+// of a split) per split and token row, each over every tiles_n-th stage.  None: t or u comes from a launch of its own.  That is so for
 // - higher ranks, whose partial sums and adapter rows cost the kernel that adds them more than the launch saved (64 x 5120 <- 13824,
 //   rank 32, forward 40.3 -> 44.1 us; 257 x 2080 <- 4104, backward 31.3 -> 32.1), and rank 16 forward, where a thread's four
 //   rows of B are 128 bytes (512 x 4096 <- 4096: 36.6 -> 38.4, 256: 30.6 -> 29.5);
@@ -95,14 +101,22 @@ inline int gemm_splits(int M, int NO, int KC)
 //   more than twice as many token rows as columns (the kernel that adds the planes takes two rows to a workgroup, whatever
 //   their length): 427 x 128 <- 32000 72 us, 91 with u beside it; 3941 x 384 <- 5120 54 and 57.  Over 4700 shapes of ranks 8 and 16
 //   the whole backward pass takes 0.87 times as long with u beside the GEMM inside these bounds, 1.00 times outside;
-// - forward, 4096 token rows and more, where the launch of its own fills the chip: 10913 x 128 <- 1024 1.14 times as long.
+// - forward, 4096 token rows and more, where the launch of its own fills the chip (10913 x 128 <- 1024: 1.14 times as long), and
+//   fewer than eight partial sums, which leave waves idle in the launch that recomputes such a t.
+inline GemmSide gemm_side(int M, int NO, int KC, int r, bool forward)
+{
+    GemmSide d;
+    const int s = gemm_splits(M, NO, KC);
+    if (s < 2 || !(r == 8 || (r == 16 && !forward))) return d;
+    d.tiles_n = (NO + GEMM_SPLIT_BN - 1) / GEMM_SPLIT_BN;
+    d.kt_split = ((KC + 63) / 64 + s - 1) / s;
+    d.per_split = d.tiles_n < d.kt_split ? d.tiles_n : d.kt_split;
+    if (forward ? M < 4096 && s * d.per_split >= 8 : (d.tiles_n > 1 && M <= 2 * GEMM_SPLIT_BN * d.tiles_n)) d.parts = s * d.per_split;
+    return d;           // parts <= splits * tiles_n, at most 256: gemm_splits() fills the compute units once
+}
 inline size_t gemm_side_floats(int M, int NO, int KC, int r, bool forward)
 {
-    const int s = gemm_splits(M, NO, KC);
-    if (s < 2 || !(r == 8 || (r == 16 && !forward))) return 0;
-    const int tiles_n = (NO + GEMM_SPLIT_BN - 1) / GEMM_SPLIT_BN, kt = ((KC + 63) / 64 + s - 1) / s;
-    if (forward ? M >= 4096 : (tiles_n < 2 || M > 2 * GEMM_SPLIT_BN * tiles_n)) return 0;
-    return (size_t)s * (tiles_n < kt ? tiles_n : kt) * M * r;
+    return (size_t)gemm_side(M, NO, KC, r, forward).parts * M * r;
 }
 // part: gemm_splits(M, NO, KC) * M * NO floats when that count exceeds 1 (NO = N, KC = K forward; NO = K, KC = N
 // backward); NULL switches splitting off.  side != NULL (gemm_side_floats() of them, more than 0): t = x A^T (u = dY B) is formed

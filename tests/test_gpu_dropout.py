@@ -119,3 +119,34 @@ def test_recomputed_t_beside_u_gives_the_same_bits(case, masked):
         got.append([layer.host_dx().copy(), layer.host_dA().copy(), layer.host_dB().copy()])
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+# the same where the forward GEMM splits its contraction and forms t beside its tiles (rank 8): t by both launches that recompute
+# it (beside u, and alone where u is formed beside the GEMM), up to 256 partial sums of t per token, a contraction that ends inside a
+# stage, a last split shorter than the tile columns (their partial sums stay empty), one tile column, many token
+# rows; and the t of a forward pass whose workspace lacks the room for the partial sums
+@pytest.mark.parametrize("case", [(256, 11008, 264, 4, "f16"), (130, 2080, 1032, 3, "bf16"), (40, 1056, 4160, 2, "f16"),
+                                  (40, 16384, 4096, 2, "bf16"), (333, 9024, 96, 4, "f16"), (3001, 4128, 72, 8, "f16"),
+                                  (300, 2080, 1368, 2, "f16")], ids=lambda c: "M{}_K{}_N{}_b{}_{}".format(*c))
+def test_recomputed_t_of_a_split_contraction_gives_the_same_bits(case):
+    import torch
+    from paper_2306_08162_amd.device import DeviceLayer
+    M, K, N, bits, dtype = case
+    inp = small_inputs(M + K + N + bits, M, K, N, bits, 32, 8, dtype)
+    announce(f"recomputed t, split contraction: {inp.cfg.name}")
+    layer = DeviceLayer(inp)
+    full = layer.workspace
+    t, dx, dB = [], [], []
+    for room in (full, full[:-256]):
+        layer.workspace = room
+        layer.forward()
+        torch.cuda.synchronize()
+        t.append(layer.host_t().copy())
+    layer.workspace = full
+    for saved in (True, False):
+        layer.backward(use_saved_t=saved)
+        torch.cuda.synchronize()
+        dx.append(layer.host_dx().copy())
+        dB.append(layer.host_dB().copy())
+    for a, b in (t, dx, dB):
+        assert np.array_equal(a, b)
