@@ -99,7 +99,7 @@ constexpr int GATHER_ROWS = 2;
 constexpr int GATHER_LDS_BYTES = 16384;
 constexpr int GATHER_LDS_K = 32768;      // one row of 64 KB: the most a launch gets without asking for more
 constexpr int GATHER_BATCH = 4;          // pieces a thread requests before it lays the first down
-template <int T>
+template <int T, bool AHEAD>
 __global__ __launch_bounds__(T) void gather_columns_lds_kernel(const uint16_t *__restrict__ src,
                                                                const int32_t *__restrict__ index,
                                                                uint16_t *__restrict__ dst, int M, int K, int R)
@@ -109,23 +109,25 @@ __global__ __launch_bounds__(T) void gather_columns_lds_kernel(const uint16_t *_
     const int nrows = m0 + R <= M ? R : M - m0;
     const int pieces = nrows * (K / 8);                        // the rows are adjacent in memory: one flat copy
     const u32x4_t *from = reinterpret_cast<const u32x4_t *>(src + (long)m0 * K);
-    int idx[8];                                                // the first columns' sources, asked for ahead of the rows
+    constexpr int BATCH = AHEAD ? GATHER_BATCH : 1;
+    int idx[8];                                                // AHEAD: the first columns' sources, asked for ahead of the rows
     auto load_index = [&](int j0) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) idx[e] = index[j0 + e];
     };
-    if ((int)threadIdx.x * 8 < K) load_index(threadIdx.x * 8);
-    for (int p0 = threadIdx.x; p0 < pieces; p0 += GATHER_BATCH * T) {
-        u32x4_t v[GATHER_BATCH];
+    if (AHEAD && (int)threadIdx.x * 8 < K) load_index(threadIdx.x * 8);
+    for (int p0 = threadIdx.x; p0 < pieces; p0 += BATCH * T) {
+        u32x4_t v[BATCH];
 #pragma unroll
-        for (int i = 0; i < GATHER_BATCH; ++i)
+        for (int i = 0; i < BATCH; ++i)
             if (p0 + i * T < pieces) v[i] = from[p0 + i * T];
 #pragma unroll
-        for (int i = 0; i < GATHER_BATCH; ++i)
+        for (int i = 0; i < BATCH; ++i)
             if (p0 + i * T < pieces) reinterpret_cast<u32x4_t *>(rows)[p0 + i * T] = v[i];
     }
     __syncthreads();
     for (int j0 = threadIdx.x * 8; j0 < K; j0 += T * 8) {
+        if constexpr (!AHEAD) load_index(j0);
         int col[8];
         bool ok[8];
 #pragma unroll
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(T) void gather_columns_lds_kernel(const uint16_t *_
             ok[e] = (unsigned)idx[e] < (unsigned)K;
             col[e] = ok[e] ? idx[e] : 0;
         }
-        if (j0 + T * 8 < K) load_index(j0 + T * 8);
+        if (AHEAD && j0 + T * 8 < K) load_index(j0 + T * 8);
         for (int i = 0; i < nrows; ++i) {
             const uint16_t *row = rows + i * K;
             uint16_t v[8];
@@ -256,12 +258,21 @@ void launch_gather_columns(const void *src, const int32_t *index, void *dst, int
         R = R < 1 ? 1 : (R > GATHER_ROWS ? GATHER_ROWS : R);
         const dim3 grid((unsigned)((M + R - 1) / R));
         const size_t lds = (size_t)R * K * 2;
-        // a thread per eight columns, up to 1024; a single workgroup is done sooner with fewer (one row of 4096: 3.2 against 3.3 us)
+        // A thread per eight columns, up to 1024, for then a row is one request a thread (100 x 32768: 13.0 us with 256 threads, 6.7); but
+        // - rows up to 2048 columns have nothing to ask for ahead of: 2 x 256 2.47 us, 2.74 with requests ahead;
+        // - a single workgroup is done sooner with fewer (one row of 4096: 3.2 against 3.3 us);
+        // - more than 512 workgroups of 1024 threads are a second round, and with rows up to 16384 columns 512 threads, four workgroups
+        //   to a compute unit, are faster from there on (1100 x 8224: 8.6 against 8.2 us, 4096 x 9216 24.3 and 24.2);
+        // - 768 to 1536 workgroups are one round, not two, of 256 threads (1237 x 4128: 5.4 against 5.9 us, 1280 x 9216 9.2 and 9.9);
+        //   longer rows do not leave room for eight workgroups to a compute unit.
         const uint16_t *from = (const uint16_t *)src;
         uint16_t *to = (uint16_t *)dst;
-        if (M > R && K > 8192) QLORA_LAUNCH(gather_columns_lds_kernel<1024>, grid, dim3(1024), lds, s, from, index, to, M, K, R);
-        else if (M > R && K > 2048) QLORA_LAUNCH(gather_columns_lds_kernel<512>, grid, dim3(512), lds, s, from, index, to, M, K, R);
-        else QLORA_LAUNCH(gather_columns_lds_kernel<256>, grid, dim3(256), lds, s, from, index, to, M, K, R);
+        auto launch = [&](auto kern, int threads) { QLORA_LAUNCH(kern, grid, dim3(threads), lds, s, from, index, to, M, K, R); };
+        if (K <= 2048 || (M <= R && K < 4096) || (R == 1 && K < 10240 && M > 768 && M <= 1536))
+            launch(gather_columns_lds_kernel<256, false>, 256);
+        else if (M <= R) launch(gather_columns_lds_kernel<256, true>, 256);
+        else if (K <= 8192 || (K <= 16384 && M > 512)) launch(gather_columns_lds_kernel<512, true>, 512);
+        else launch(gather_columns_lds_kernel<1024, true>, 1024);
         return;
     }
     const unsigned row_blocks = (unsigned)((M + GATHER_ROWS - 1) / GATHER_ROWS);

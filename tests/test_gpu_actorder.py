@@ -144,7 +144,8 @@ def test_gather_rows_wider_than_the_lds_staging():
 
 # both sides of the workgroup sizes (2048 and 8192 columns, one or more workgroups), rows that end inside a batch of pieces, the
 # longest row that is staged; a few indexes out of range
-@pytest.mark.parametrize("M,K", [(1, 2048), (3, 2048), (3, 2080), (1, 4096), (5, 8192), (3, 8224), (2, 32768), (3, 32)])
+@pytest.mark.parametrize("M,K", [(1, 2048), (3, 2048), (3, 2080), (1, 4096), (5, 8192), (3, 8224), (2, 32768), (3, 32),
+                                 (1, 2080), (1, 4128), (513, 8224), (770, 4128), (1536, 9216), (1537, 4128)])
 def test_gathered_columns_at_the_workgroup_sizes(M, K):
     import torch
     from paper_2306_08162_amd import binding as ql
