@@ -758,11 +758,6 @@ void launch_lora_u(const void *dy, const void *B, void *u, int M, int N, int r, 
 void launch_lora_u_and_down(const void *dy, const void *B, void *u, const void *x, const void *A, void *t, int M, int N, int K,
                             int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s, const GemmSide &order)
 {
-    if (M >= 16 * 256) {        // sixteen rows to a workgroup, and enough of them for either product
-        launch_lora_u(dy, B, u, M, N, r, bf16, s);
-        launch_lora_down(x, A, t, M, K, r, bf16, keep, keep_scale, s, nullptr, order);
-        return;
-    }
     const SkinnyPair a{{(const uint16_t *)dy, (const uint16_t *)x}, {(const uint16_t *)B, (const uint16_t *)A},
                        {(uint16_t *)u, (uint16_t *)t}, {N, K}, M, r, (const uint8_t *)keep, keep_scale, order};
     if (keep) {

@@ -67,7 +67,9 @@ void launch_lora_dx_masked(void *dx, const void *u, const void *A, const uint32_
                            bool bf16, hipStream_t s);
 // u[M,r] = dy[M,N] B[N,r]
 void launch_lora_u(const void *dy, const void *B, void *u, int M, int N, int r, bool bf16, hipStream_t s);
-// both (t as launch_lora_down without planes), one launch below 4096 token rows
+// both (t as launch_lora_down without planes) in one launch, fewer than LORA_PAIR_END token rows: from there on workgroups of
+// sixteen rows fill the chip with either product alone
+constexpr int LORA_PAIR_END = 16 * 256;
 void launch_lora_u_and_down(const void *dy, const void *B, void *u, const void *x, const void *A, void *t, int M, int N, int K,
                             int r, bool bf16, const uint32_t *keep, float keep_scale, hipStream_t s, const GemmSide &order);
 // dB[N,r] = sc * dy[M,N]^T t[M,r] and dA[r,K] = sc * u[M,r]^T x[M,K], one launch for both, sums in a fixed order.
