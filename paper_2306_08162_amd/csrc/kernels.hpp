@@ -99,12 +99,13 @@ inline int gemm_splits(int M, int NO, int KC)
 // - higher ranks, whose partial sums and adapter rows cost the kernel that adds them more than the launch saved (64 x 5120 <- 13824,
 //   rank 32, forward 40.3 -> 44.1 us; 257 x 2080 <- 4104, backward 31.3 -> 32.1), and rank 16 forward, where a thread's four
 //   rows of B are 128 bytes (512 x 4096 <- 4096: 36.6 -> 38.4, 256: 30.6 -> 29.5);
-// - backward, outputs of one tile column (its workgroups form u in all of their stages, from B's rows two bytes a lane) and
-//   more than twice as many token rows as columns (the kernel that adds the planes takes two rows to a workgroup, whatever
-//   their length): 427 x 128 <- 32000 72 us, 91 with u beside it; 3941 x 384 <- 5120 54 and 57.  Over 4700 shapes of ranks 8 and 16
-//   the whole backward pass takes 0.87 times as long with u beside the GEMM inside these bounds, 1.00 times outside;
-// - forward, 4096 token rows and more, where the launch of its own fills the chip (10913 x 128 <- 1024: 1.14 times as long), and
-//   fewer than eight partial sums, which leave waves idle in the launch that recomputes such a t.
+// - backward, outputs of one tile column (its workgroups form u in all of their stages, from B's rows two bytes a lane: 427 x 128 <-
+//   32000 72 us, 91 with u beside it), and of two or three with up to four splits and more than twice as many token rows as
+//   columns (the kernel that adds the planes takes two rows to a workgroup, whatever their length: 3941 x 384 <- 5120 54 and 57 us).
+//   With five splits, or four tile columns, the pass takes 0.80 to 0.97 times as long with u beside the GEMM;
+// - forward, fewer than eight partial sums, which come of outputs up to 384 columns and would leave waves idle in the launch that
+//   recomputes such a t; among them are the calls, of 4096 token rows and more with short contractions, that a t beside the GEMM
+//   makes slower (10913 x 128 <- 1024: 1.14 times as long).
 inline GemmSide gemm_side(int M, int NO, int KC, int r, bool forward)
 {
     GemmSide d;
@@ -113,7 +114,8 @@ inline GemmSide gemm_side(int M, int NO, int KC, int r, bool forward)
     d.tiles_n = (NO + GEMM_SPLIT_BN - 1) / GEMM_SPLIT_BN;
     d.kt_split = ((KC + 63) / 64 + s - 1) / s;
     d.per_split = d.tiles_n < d.kt_split ? d.tiles_n : d.kt_split;
-    if (forward ? M < 4096 && s * d.per_split >= 8 : (d.tiles_n > 1 && M <= 2 * GEMM_SPLIT_BN * d.tiles_n)) d.parts = s * d.per_split;
+    if (forward ? s * d.per_split >= 8 : d.tiles_n >= 4 || (d.tiles_n > 1 && (s >= 5 || M <= 2 * GEMM_SPLIT_BN * d.tiles_n)))
+        d.parts = s * d.per_split;
     return d;           // parts <= splits * tiles_n, at most 256: gemm_splits() fills the compute units once
 }
 inline size_t gemm_side_floats(int M, int NO, int KC, int r, bool forward)

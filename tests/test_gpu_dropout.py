@@ -126,7 +126,7 @@ def test_recomputed_t_beside_u_gives_the_same_bits(case, masked):
 # stage, a last split shorter than the tile columns (their partial sums stay empty), one tile column, many token
 # rows; and the t of a forward pass whose workspace lacks the room for the partial sums
 @pytest.mark.parametrize("case", [(256, 11008, 264, 4, "f16"), (130, 2080, 1032, 3, "bf16"), (40, 1056, 4160, 2, "f16"),
-                                  (40, 16384, 4096, 2, "bf16"), (333, 9024, 96, 4, "f16"), (3001, 4128, 72, 8, "f16"),
+                                  (40, 16384, 4096, 2, "bf16"), (333, 9024, 96, 4, "f16"), (3001, 4128, 72, 8, "f16"), (4096, 4128, 72, 2, "f16"),
                                   (300, 2080, 1368, 2, "f16")], ids=lambda c: "M{}_K{}_N{}_b{}_{}".format(*c))
 def test_recomputed_t_of_a_split_contraction_gives_the_same_bits(case):
     import torch
