@@ -38,26 +38,65 @@ SIDE = [(33, 4096, 512, 4, 8, "f16"), (130, 2080, 1032, 3, 8, "bf16"), (40, 1024
         (200, 1056, 2056, 2, 16, "bf16"), (28, 1024, 1024, 8, 8, "f16"), (129, 2048, 136, 8, 8, "f16")]
 
 
+PATTERN = 0x5a
+
+
+def _in_room(inp, room, alloc, packed_zeros=False):
+    """Outputs of both passes with the first `room` bytes of `alloc`, which holds PATTERN, as their workspace."""
+    import torch
+    import oracle
+    from paper_2306_08162_amd.device import DeviceLayer
+    layer = DeviceLayer(inp)
+    if packed_zeros:
+        layer.use_packed_zeros(oracle.pack_zeros(inp.zeros, inp.cfg.bits))
+    alloc.fill_(PATTERN)
+    layer.workspace = alloc[:room]
+    layer.forward()
+    layer.backward()
+    torch.cuda.synchronize()
+    assert bool((alloc[room:] == PATTERN).all()), f"bytes behind the {room} of the workspace were written"
+    return {"y": layer.host_y().copy(), "t": layer.host_t().copy(), "dx": layer.host_dx().copy(), "dA": layer.host_dA().copy(),
+            "dB": layer.host_dB().copy()}
+
+
 @pytest.mark.parametrize("case", SIDE, ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(*c))
 def test_adapter_products_beside_a_split_gemm(case):
     import torch
-    from paper_2306_08162_amd.device import DeviceLayer
+    import oracle
+    from paper_2306_08162_amd import binding as ql
     M, K, N, bits, r, dtype = case
     inp = small_inputs(M + K + N + bits, M, K, N, bits, 32, r, dtype)
     check_layer(inp)
-    # a workspace without the room for the partial sums of t and u: they come from launches of their own.  Both forms round
-    # the same fp32 sums, taken in another order, to 16 bits: half a unit in the last place each
+    # the room without the partial sums of t and u: what the layer needs without an adapter, and t and u
     announce(f"smaller workspace: {inp.cfg.name}")
-    full, less = DeviceLayer(inp), DeviceLayer(inp)
-    less.workspace = less.workspace[:-256]
-    for layer in (full, less):
-        layer.forward()
-        layer.backward()
-    torch.cuda.synchronize()
-    import oracle
-    for name in ("host_y", "host_dx"):
-        a, b = (np.asarray(oracle.widen(getattr(l, name)(), dtype), np.float64) for l in (full, less))
-        assert rel_fro(a, b) <= unit_roundoff(dtype), name
+    total = ql.qlora_workspace_bytes(M, N, K, bits, 32, r)
+    base = ql.qlora_workspace_bytes(M, N, K, bits, 32, 0) + 2 * ((M * r * 2 + 255) // 256 * 256)
+    zeros = (N * (K // 32) + 255) // 256 * 256
+    assert base < total and ql.qlora_workspace_bytes_zp(M, N, K, bits, 32, r) == total + zeros
+    alloc = torch.empty(total + zeros + 4096, dtype=torch.uint8, device="cuda:0")
+    full = _in_room(inp, total, alloc)
+    assert bool((alloc[base:total] != PATTERN).any()), "t and u were formed by launches of their own"
+    less = _in_room(inp, base, alloc)
+    with pytest.raises(ql.QLoraError):
+        _in_room(inp, base - 256, alloc)
+    # t and, through it, dB: the same bits.  y, dx: the same fp32 sums in another order, half a unit in the last place each.  dA:
+    # of u rounded so, at most a unit in the last place (two roundoffs) apart
+    for name, got in full.items():
+        if name in ("t", "dB"):
+            assert np.array_equal(got, less[name]), name
+        elif name == "dA":
+            assert rel_fro(less[name], got) <= 2 * unit_roundoff(dtype), name
+        else:
+            wide = [np.asarray(oracle.widen(v, dtype), np.float64) for v in (less[name], got)]
+            assert rel_fro(*wide) <= unit_roundoff(dtype), name
+    # bit-packed zero-points, unpacked behind whichever of the two the buffer has room for: the bits of the calls above
+    announce(f"smaller workspace, packed zero-points: {inp.cfg.name}")
+    for room, want in ((total + zeros, full), (total + zeros - 256, less), (base + zeros, less)):
+        got = _in_room(inp, room, alloc, packed_zeros=True)
+        if room == total + zeros - 256:
+            assert bool((alloc[base + zeros:] == PATTERN).all())
+        for name in want:
+            assert np.array_equal(got[name], want[name]), (name, room)
 
 
 # an infinity among the last elements of a contraction that ends inside a stage: it reaches t (u) as an infinity of the other

@@ -18,6 +18,8 @@ CASES = [
     (257, 1024, 520, 8, 128, 64, 32, "bf16"),
     (131, 512, 136, 4, 64, 24, 16, "f16"),
     (9, 512, 200, 8, 128, 64, 56, "f16"),
+    (200, 1056, 2056, 2, 32, 16, 8, "bf16"),     # rank 16, split contraction: u formed beside the GEMM, t saved and recomputed
+    (131, 2080, 1032, 3, 32, 16, 8, "f16"),
 ]
 
 
