@@ -65,6 +65,16 @@ __device__ __forceinline__ uint32_t spread_byte(uint32_t x, int b)
     return __builtin_amdgcn_perm(0x64006400u, x, 0x05000500u | ((uint32_t)b << 16) | (uint32_t)b);
 }
 
+// (x & mask) | magic in one instruction: the mask from a scalar register, the magic from a vector register (as literals
+// the two constants would take two instructions; small-token backward pass, fp16, 16 tokens, gate and up: INT2 23.9 -> 22.7 us,
+// INT4 30.8 -> 30.2)
+__device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t magic)
+{
+    uint32_t d;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "s"(mask), "v"(magic));
+    return d;
+}
+
 __device__ __forceinline__ uint32_t h2_bits(half2_t v) { return __builtin_bit_cast(uint32_t, v); }
 
 // SCALE false: the exact integers q - z are returned and the caller applies the group's scale to its sums

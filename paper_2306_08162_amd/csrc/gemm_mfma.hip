@@ -402,8 +402,8 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
     static_assert(WU == 1, "one unit per staging thread and stage");
     constexpr int UPR = BN / 32;
     const int t_row = (stid >> 6) * (64 / UPR) + (stid & 63) / (8 * UPR) * 8 + (stid & 7), t_unit = (stid >> 3) % UPR;
-    auto unit_row = [&](int kt, int i) { return TRANS ? (kt_first + kt) * BK + t_row : col0 + (stid >> 1); };
-    auto unit_col = [&](int kt, int i) { return TRANS ? col0 + t_unit * 32 : (kt_first + kt) * BK + (stid & 1) * 32; };
+    auto unit_row = [&](int kt) { return TRANS ? (kt_first + kt) * BK + t_row : col0 + (stid >> 1); };
+    auto unit_col = [&](int kt) { return TRANS ? col0 + t_unit * 32 : (kt_first + kt) * BK + (stid & 1) * 32; };
     // global -> registers for stage kt.  Branch-free: every address is clamped into the valid range and
     // whatever lies beyond the contraction length (or beyond the weight's rows / columns) is neutralised by a
     // zero scale, so stages past the end may be fetched and staged harmlessly.  SYM: a uniform base and one register per
@@ -416,13 +416,13 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
 #pragma unroll
         for (int i = 0; i < WU; ++i) {
             if constexpr (SYM) {
-                const uint32_t n = (uint32_t)min(unit_row(kt, i), a.N - 1), q = (uint32_t)min(unit_col(kt, i), a.K - 32) >> 5;
+                const uint32_t n = (uint32_t)min(unit_row(kt), a.N - 1), q = (uint32_t)min(unit_col(kt), a.K - 32) >> 5;
                 load_unit<BITS>((const uint32_t *)((const uint8_t *)a.packed + (n * row_bytes + q * (BITS * 4u))), rg.w[i]);
                 const uint32_t gi = n * (uint32_t)ng + (__umulhi(q, a.g32_magic) + (q & g32_one));
                 rg.s[i] = *(const uint16_t *)((const uint8_t *)a.scales + gi * 2u);
                 rg.z[i] = *(a.zeros + gi);
             } else {
-                int n = unit_row(kt, i), k0 = unit_col(kt, i);
+                int n = unit_row(kt), k0 = unit_col(kt);
                 rg.ok[i] = TRANS ? n < a.N && k0 < a.K : k0 < a.K;
                 n = min(n, a.N - 1);
                 k0 = min(k0, a.K - 32);
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(WM * WN * 64 + (SYM ? 0 : STAGERS)) void qgemm_kern
         const int u = stid + NSTG * i;
         DequantConst<BITS, BF16> dq;
         bool ok;
-        if constexpr (SYM) ok = TRANS ? unit_row(kt, i) < a.N && unit_col(kt, i) < a.K : unit_col(kt, i) < a.K;
+        if constexpr (SYM) ok = TRANS ? unit_row(kt) < a.N && unit_col(kt) < a.K : unit_col(kt) < a.K;
         else ok = rg.ok[i];
         uint32_t sr = rg.s[i], zr = rg.z[i];
         if constexpr (TIGHT) asm volatile("" : "+v"(sr), "+v"(zr));      // not kept from one part to the next

@@ -45,15 +45,6 @@ __device__ __forceinline__ uint32_t code_of(const uint32_t (&w)[WORDS], int c)
     return v & mask;
 }
 
-// (x & mask) | magic as one instruction: the mask from a scalar register, the magic from a vector register (the compiler takes
-// two: fp16, 16 tokens, gate and up INT2 23.9 -> 22.7 us, INT4 30.8 -> 30.2)
-__device__ __forceinline__ uint32_t rows_and_or(uint32_t x, uint32_t mask, uint32_t magic)
-{
-    uint32_t d;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "s"(mask), "v"(magic));
-    return d;
-}
-
 // fp16: column c of eight consecutive weight rows as one MFMA fragment (element e = row e).  Rows are handled in
 // pairs: one byte permute drops the code of both rows into the mantissas of (1024.0, 1024.0), at bit p of each
 // half; a packed fma with (2^-p, -(1024 * 2^-p + z)) leaves the exact integers q - z and a packed multiply applies
@@ -80,7 +71,7 @@ __device__ __forceinline__ u16x8_t dequant_rows8_f16(const uint32_t (&w)[8][WORD
             hi = __builtin_amdgcn_alignbit(w[2 * i + 1][wi + 1 < WORDS ? wi + 1 : wi], hi, (uint32_t)sh);
         }
         const uint32_t bits = BITS == 8 ? __builtin_amdgcn_perm(hi, lo, sel) | 0x64006400u
-                                        : rows_and_or(__builtin_amdgcn_perm(hi, lo, sel), mask2, 0x64006400u);
+                                        : and_or(__builtin_amdgcn_perm(hi, lo, sel), mask2, 0x64006400u);
         const half2_t h = __builtin_bit_cast(half2_t, bits);
         out[i] = __builtin_bit_cast(uint32_t, (h * mul2 + (nz2[i] + off2)) * s2[i]);
     }
@@ -94,6 +85,7 @@ __device__ __forceinline__ u16x8_t dequant_rows8_f16(const uint32_t (&w)[8][WORD
 // backward pass: gate and up INT2 30.1 -> 25.9 us, INT4 34.7 -> 32.1, INT8 36.5 -> 35.8; q INT2 14.9 -> 14.0).
 template <int BITS, int WORDS>
 struct RowsConst {
+    static_assert(BITS == 2 || BITS == 4 || BITS == 8, "a code lies in one byte");
     static constexpr int NP = BITS == 2 ? 4 : (BITS == 4 ? 2 : 1);      // positions p = BITS i of a code in its byte
     float mul[NP][8], off[NP][8];
     __device__ __forceinline__ void set(int e, float s, float z)
@@ -122,7 +114,7 @@ __device__ __forceinline__ u16x8_t dequant_rows8_bf16(const uint32_t (&w)[8][WOR
                          __builtin_fmaf((float)((hi >> (8 * bb)) & 0xffu), k.mul[0][2 * h + 1], k.off[0][2 * h + 1])};
         } else {
             const uint32_t sel = (uint32_t)bb | 0x0C00u | ((uint32_t)(4 + bb) << 16) | 0x0C000000u, m1 = ((1u << BITS) - 1u) << p;
-            const half2_t v = __builtin_bit_cast(half2_t, rows_and_or(__builtin_amdgcn_perm(hi, lo, sel), m1 | (m1 << 16), 0x64006400u));
+            const half2_t v = __builtin_bit_cast(half2_t, and_or(__builtin_amdgcn_perm(hi, lo, sel), m1 | (m1 << 16), 0x64006400u));
             f = float2_t{__builtin_fmaf((float)v[0], k.mul[i][2 * h], k.off[i][2 * h]),
                          __builtin_fmaf((float)v[1], k.mul[i][2 * h + 1], k.off[i][2 * h + 1])};
         }
@@ -565,7 +557,7 @@ __device__ __forceinline__ void gemv_bwd_staged_body(const BwdArgs &a, const int
 }
 
 // u = dY B of one row slice (the workgroup past the last column block of every slice): B^T fragments gathered
-// column-wise, four 32-row chunks in flight per wave
+// column-wise, a 32-row chunk per wave at a time
 template <bool BF16, int MB>
 __device__ __forceinline__ void gemv_bwd_u_body(const BwdArgs &a, const int sp_local, const int sp)
 {

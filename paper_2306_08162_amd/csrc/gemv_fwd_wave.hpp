@@ -49,15 +49,6 @@ struct FwConst {
     }
 };
 
-// (x & mask) | magic in one instruction: the mask from a scalar register, the magic from a vector register (as literals
-// the two constants would take two instructions)
-__device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t magic)
-{
-    uint32_t d;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "s"(mask), "v"(magic));
-    return d;
-}
-
 template <int BITS, bool BF16>
 __device__ __forceinline__ u16x8_t fw_dequant8(const uint32_t (&w)[BITS], int part, const FwConst<BITS, BF16> &c)
 {
