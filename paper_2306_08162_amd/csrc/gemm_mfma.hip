@@ -1013,10 +1013,13 @@ void launch_tiles(GemmArgs &a, uint16_t *side_out, hipStream_t s)
     // win against two, as in fp16 four do against three: 595 tokens to 11008 columns are 430 or 258 tiles, forward from 4096
     // 99.8 -> 72.8 us, backward from 5120 121.8 -> 87.0; 1350 tokens 946 or 516, forward 162.7 -> 147.4 (bf16, whose 128-row tiles
     // are slower, 0.94 to 1.03 times as long).  With more rounds the last one is too small a part of the launch (six against four,
-    // five and more: 1.04 to 1.4 times as long).
+    // five and more: 1.04 to 1.4 times as long).  Not forward with more packed words than the 256 MB of the Infinity Cache, which the
+    // third tile row reads from HBM again: four rounds 1.09 to 1.12 times as long as three (306 tokens, 34816 <- 11328, INT8: 552
+    // and 493 us), up to there 0.89 to 1.01.
     if constexpr (BM == 256) {
         const int tall = (a.M + 255) / 256 * a.tiles_n, flat = (a.M + 127) / 128 * a.tiles_n;
-        if (flat <= 256 || (flat <= 512 && tall > 256) || (!BF16 && flat <= 1024 && tall > 512)) {
+        const bool cached = (long long)NO * KC * BITS <= (2ll << 30);
+        if (flat <= 256 || (flat <= 512 && tall > 256) || (!BF16 && flat <= 1024 && tall > 512 && (TRANS || cached))) {
             a.tiles_m = (a.M + 127) / 128;
             if constexpr (TRANS) {
                 if (a.keep) {           // the masked epilogue needs the whole contraction in one workgroup
@@ -1062,13 +1065,19 @@ void launch_tiles(GemmArgs &a, uint16_t *side_out, hipStream_t s)
     // One round of them, up to 4/5 full, beside two of the smaller tiles: fp16 forward 0.83 to 0.99 times as long (1110 tokens,
     // 8192 <- 2048, INT3 55 -> 51 us), fp16 backward with 2 and 4 bits 0.93 to 0.98 (738 tokens, 13824 <- 11008: 260 -> 230 us);
     // 0.95 to 1.04 where it is fuller, where the backward pass unpacks 3 or 8 bits, and in bf16.  Contractions of 128 to 768: 105
-    // of 108 calls 0.75 to 0.99 times as long, three 1.01 to 1.04 (1740 tokens, 7216 <- 384, INT4, the most).
+    // of 108 calls 0.75 to 0.99 times as long, three 1.01 to 1.04 (1740 tokens, 7216 <- 384, INT4, the most); 1040 calls of other
+    // lengths 0.65 to 1.03, seven with 8 bits forward up to 1.08 (129 tokens, 34048 <- 12096).
+    // "Nearly full" is 4/5 of a round where a tile's fixed part counts most: a contraction of one stage (the smaller tiles 0.99 to 1.10
+    // times as long), and ranks above 32, whose rows the smaller tiles fetch after their last stage only, up to 32 stages (1.06 to
+    // 1.44 times as long up to 8: 804 tokens, 52800 <- 64, rank 64 48 and 65 us; 0.99 to 1.10 up to 32).  Elsewhere it is 17/20: between
+    // the two the smaller tiles take 0.77 to 1.06 times as long, 0.93 in the mean of 377 calls (one 1.15: 6149 tokens, 6208 <- 384).
     {
         const int tn = (NO + 255) / 256, tiles = a.tiles_m * tn, rounds = (tiles + 255) / 256;
         const int small_rounds = (a.tiles_m * a.tiles_n + 255) / 256;
         const bool half = 2 * rounds <= small_rounds, full = tiles * 10 >= rounds * 256 * 8;
+        const bool fixed = KC <= BK || (a.r > 32 && KC <= 32 * BK);
         bool take;
-        if (tiles >= 256) take = half ? !BF16 || full : tiles * 20 >= rounds * 256 * 17;
+        if (tiles >= 256) take = half ? !BF16 || full : (fixed ? full : tiles * 20 >= rounds * 256 * 17);
         else take = half && !full && !BF16 && (!TRANS || BITS == 2 || BITS == 4);
         if (take) {
             a.tiles_n = tn;

@@ -32,6 +32,17 @@ def test_tile_shape_by_rounds(case):
     check_layer(small_inputs(M + K + N + bits, M, K, N, bits, 32, 8, dtype))
 
 
+# 624 of 768 places of 256 x 256 tiles: taken with one stage, or with a rank above 32; 256 x 128 tiles at two stages and rank 8
+NEARLY_FULL = [(1290, 64, 26376, 4, 64, "bf16"), (1290, 26400, 64, 2, 8, "f16"), (1290, 128, 26376, 3, 48, "f16"),
+               (1290, 128, 26376, 8, 8, "bf16")]
+
+
+@pytest.mark.parametrize("case", NEARLY_FULL, ids=lambda c: "M{}_K{}_N{}_b{}_r{}_{}".format(*c))
+def test_nearly_full_rounds_of_large_tiles(case):
+    M, K, N, bits, r, dtype = case
+    check_layer(small_inputs(M + K + N + bits, M, K, N, bits, 32, r, dtype))
+
+
 # split contractions at ranks 8 and 16: fewer tile columns than stages of a split (33), a contraction that ends inside a stage
 # (2080, 1032), a last split shorter than the tile columns (4160), 8-bit codes at 28 tokens (tiled backward pass only)
 SIDE = [(33, 4096, 512, 4, 8, "f16"), (130, 2080, 1032, 3, 8, "bf16"), (40, 1024, 4160, 2, 16, "f16"),
