@@ -100,12 +100,13 @@ inline int gemm_splits(int M, int NO, int KC)
 //   rank 32, forward 40.3 -> 44.1 us; 257 x 2080 <- 4104, backward 31.3 -> 32.1), and rank 16 forward, where a thread's four
 //   rows of B are 128 bytes (512 x 4096 <- 4096: 36.6 -> 38.4, 256: 30.6 -> 29.5);
 // - backward, outputs of one tile column (its workgroups form u in all of their stages, from B's rows two bytes a lane: 427 x 128 <-
-//   32000 72 us, 91 with u beside it), and of two or three with up to four splits and more than twice as many token rows as
-//   columns (the kernel that adds the planes takes two rows to a workgroup, whatever their length: 3941 x 384 <- 5120 54 and 57 us).
-//   With five splits, or four tile columns, the pass takes 0.80 to 0.97 times as long with u beside the GEMM;
-// - forward, fewer than eight partial sums, which come of outputs up to 384 columns and would leave waves idle in the launch that
-//   recomputes such a t; among them are the calls, of 4096 token rows and more with short contractions, that a t beside the GEMM
-//   makes slower (10913 x 128 <- 1024: 1.14 times as long).
+//   32000 72 us, 91 with u beside it) except up to 128 token rows with more than 12 stages a split (0.97 times as long), and of two
+//   with two splits and more than 512 token rows (the kernel that adds the planes takes two rows to a workgroup, whatever their
+//   length: 1.03 to 1.07 times as long).  With more of either the pass takes 0.80 to 1.01 times as long, by the mean of each size;
+// - forward, two and three partial sums of up to 64 stages: t beside the GEMM takes 0.86 to 0.97 times as long (61 -> 52 us at most),
+//   but the launch that recomputes such a t, a wave to a partial sum, leaves the other waves idle, and the backward pass takes 1.12 to
+//   1.13 times as long (112 -> 126 us).  Longer ones: 208 -> 162 us forward, 352 -> 377 backward; four to seven partial sums 0.75 to
+//   0.93 times as long forward, 0.98 to 1.06 backward.
 inline GemmSide gemm_side(int M, int NO, int KC, int r, bool forward)
 {
     GemmSide d;
@@ -114,8 +115,12 @@ inline GemmSide gemm_side(int M, int NO, int KC, int r, bool forward)
     d.tiles_n = (NO + GEMM_SPLIT_BN - 1) / GEMM_SPLIT_BN;
     d.kt_split = ((KC + 63) / 64 + s - 1) / s;
     d.per_split = d.tiles_n < d.kt_split ? d.tiles_n : d.kt_split;
-    if (forward ? s * d.per_split >= 8 : d.tiles_n >= 4 || (d.tiles_n > 1 && (s >= 5 || M <= 2 * GEMM_SPLIT_BN * d.tiles_n)))
-        d.parts = s * d.per_split;
+    const int parts = s * d.per_split;
+    const bool take = forward          ? parts >= 4 || d.kt_split > 64
+                      : d.tiles_n == 1 ? M <= 128 && d.kt_split > 12
+                      : d.tiles_n == 2 ? s > 2 || M <= 4 * GEMM_SPLIT_BN
+                                       : true;
+    if (take) d.parts = parts;
     return d;           // parts <= splits * tiles_n, at most 256: gemm_splits() fills the compute units once
 }
 inline size_t gemm_side_floats(int M, int NO, int KC, int r, bool forward)

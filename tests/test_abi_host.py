@@ -57,14 +57,15 @@ def test_workspace_bytes():
 
 
 # (M, N, K, rank, does the workspace hold partial sums of t or u): a split contraction of either pass forms them beside the GEMM at
-# ranks 8 and (u) 16; not u of one tile column, or of two or three with up to four splits and more than twice as many token rows as
-# columns, nor t in fewer than eight partial sums
+# ranks 8 and (u) 16; not u of one tile column above 128 token rows or up to 12 stages a split, or of two with two splits above 512
+# rows, nor t in two or three partial sums of up to 64 stages
 @pytest.mark.parametrize("M,N,K,r,side", [
     (256, 4096, 4096, 8, True), (256, 4096, 4096, 16, True), (256, 4096, 4096, 32, False), (2048, 4096, 4096, 8, False),
-    (427, 32000, 128, 8, False), (28, 1024, 64, 8, False), (427, 32000, 192, 8, True), (512, 32000, 256, 8, True),
-    (513, 32000, 256, 8, True), (1000, 2048, 256, 8, False), (3941, 5120, 384, 16, False), (768, 5120, 384, 16, True),
-    (3941, 5120, 512, 16, True), (4096, 128, 4096, 8, True), (1024, 128, 3584, 8, False), (4097, 128, 8192, 8, False),
-    (10913, 128, 1024, 8, False), (16, 4096, 4096, 8, False)])
+    (128, 32000, 128, 8, True), (129, 32000, 128, 8, False), (28, 7168, 64, 8, True), (28, 1024, 64, 8, False),
+    (427, 32000, 192, 8, True), (513, 32000, 256, 8, True), (1000, 2048, 256, 8, True), (512, 1024, 256, 8, True),
+    (513, 1024, 256, 8, False), (3941, 5120, 384, 16, True), (3941, 5120, 512, 16, True), (4096, 128, 4096, 8, True),
+    (1024, 128, 3584, 8, True), (4097, 128, 8192, 8, True), (10913, 128, 1024, 8, False), (10913, 128, 8192, 8, False),
+    (10913, 128, 8256, 8, True), (16, 4096, 4096, 8, False)])
 def test_workspace_room_for_adapter_partial_sums(M, N, K, r, side):
     def room(rank):
         return ql.qlora_workspace_bytes(M, N, K, 4, 64, rank)

@@ -124,9 +124,10 @@ def test_recomputed_t_beside_u_gives_the_same_bits(case, masked):
 # the same where the forward GEMM splits its contraction and forms t beside its tiles (rank 8): t by both launches that recompute
 # it (beside u, and alone where u is formed beside the GEMM), up to 256 partial sums of t per token, a contraction that ends inside a
 # stage, a last split shorter than the tile columns (their partial sums stay empty), one tile column, many token
-# rows; and the t of a forward pass whose workspace lacks the room for the partial sums
+# rows, four and three partial sums; and the t of a forward pass whose workspace lacks the room for the partial sums
 @pytest.mark.parametrize("case", [(256, 11008, 264, 4, "f16"), (130, 2080, 1032, 3, "bf16"), (40, 1056, 4160, 2, "f16"),
                                   (40, 16384, 4096, 2, "bf16"), (333, 9024, 96, 4, "f16"), (3001, 4128, 72, 8, "f16"), (4096, 4128, 72, 2, "f16"),
+                                  (1290, 2080, 72, 4, "f16"), (8193, 12512, 72, 2, "bf16"),
                                   (300, 2080, 1368, 2, "f16")], ids=lambda c: "M{}_K{}_N{}_b{}_{}".format(*c))
 def test_recomputed_t_of_a_split_contraction_gives_the_same_bits(case):
     import torch

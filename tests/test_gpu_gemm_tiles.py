@@ -44,9 +44,11 @@ def test_nearly_full_rounds_of_large_tiles(case):
 
 
 # split contractions at ranks 8 and 16: fewer tile columns than stages of a split (33), a contraction that ends inside a stage
-# (2080, 1032), a last split shorter than the tile columns (4160), 8-bit codes at 28 tokens (tiled backward pass only)
+# (2080, 1032), a last split shorter than the tile columns (4160), 8-bit codes at 28 tokens (tiled backward pass only), u
+# with one tile column, with two and more token rows, t in four partial sums
 SIDE = [(33, 4096, 512, 4, 8, "f16"), (130, 2080, 1032, 3, 8, "bf16"), (40, 1024, 4160, 2, 16, "f16"),
-        (200, 1056, 2056, 2, 16, "bf16"), (28, 1024, 1024, 8, 8, "f16"), (129, 2048, 136, 8, 8, "f16")]
+        (200, 1056, 2056, 2, 16, "bf16"), (28, 1024, 1024, 8, 8, "f16"), (129, 2048, 136, 8, 8, "f16"),
+        (100, 96, 6664, 4, 16, "f16"), (600, 224, 2056, 3, 8, "bf16"), (1290, 2080, 72, 2, 8, "f16")]
 
 
 PATTERN = 0x5a
